@@ -1238,6 +1238,9 @@ fkv_status fkv_attention_mass(const fkv_shape *shape, const void *Q, const void 
     a.n_qtiles = (a.Lq + fkv::kAttnRowsBf16 - 1) / fkv::kAttnRowsBf16;
     a.n_items = a.n_heads * a.n_qtiles;
     a.part = (float *)workspace;
+    int blocks = 0;
+    if ((st = balanced_blocks(&blocks)) != FKV_OK) return st;
+    a.n_blocks = 2 * blocks;   // two workgroups per CU
     a.mass_F = shape->frame_tokens;
     a.mass_bins = n_bins;
     a.mass_acc = accumulate;

@@ -716,48 +716,47 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnArgs a) {
 
 // ------------------------------------------------------------ attention mass
 // Offline head profiling (Sec. 4.1, Eq. 1) needs, per head, the attention mass
-// each block of F keys of [Kc[0:kv_len]; K_cur] receives: the sum over all
-// query rows of the softmax probabilities exp(scale*q.k - lse_row), with lse
-// from fkv_chunk_attention over the same keys.  Workgroup = (256-row query
-// tile, head), 8 waves x 32 rows.  Per 64-key tile the waves compute S^T with
-// the attention kernel's score product (same MFMA sequence, so the same fp32
-// scores), form the probabilities, and for every key block the tile touches
-// reduce their sum across the wave with a fixed butterfly; lane 0 adds it to
-// the wave's own bin array in the workspace, so the result is deterministic.
+// each block (bin) of F keys of [Kc[0:kv_len]; K_cur] receives: the sum over
+// all query rows of the softmax probabilities exp(scale*q.k - lse_row), with
+// lse from fkv_chunk_attention over the same keys.
+//
+// Work unit = (head, 256-row query tile, bin), 8 waves x 32 rows; the units in
+// that order are split evenly over two workgroups per CU (every unit costs the
+// same), so a unit is computed by one workgroup and its eight wave sums are
+// written once: no read-modify-write, a fixed order, the same bits on every
+// run.  A bin's keys are read in tiles of 64 from its first key on (its last
+// tile is masked), double buffered in LDS, the next tile's loads in flight
+// during the products; a workgroup streams the consecutive bins of a query
+// tile without draining.  Per tile the waves compute S^T with the attention
+// kernel's score product (the same MFMA sequence, so the same fp32 scores) and
+// every lane adds its probabilities in fp32; the lanes are summed (a fixed
+// butterfly) once per bin.
+//
+// Bound: the VALU -- per 64-key tile a wave issues 32 exponentials (quarter
+// rate), 32 FMAs and 32 adds against 16 products (512 cycles); four waves per
+// SIMD overlap the two.  480P, 12 heads over the whole 21-frame history (37440
+// keys): 533 us, 1.01 PFLOP/s of score products; 1350 us with one workgroup
+// per query tile, staging and products in turn, and every tile's sum reduced
+// and added to its bin in memory.  Finalize 4 us (28 us with one workgroup per
+// head walking each bin's sums in series).
 __device__ __forceinline__ float wave_sum_f(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
 
+__device__ __forceinline__ int mass_bins_of(const AttnArgs &a, int h) {
+    return (head_kvl(a, h) + a.Lq + a.mass_F - 1) / a.mass_F;
+}
+
 template <int D>
-__global__ __launch_bounds__(kThreads) void attn_mass_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void attn_mass_kernel(AttnArgs a) {
     using C = Cfg<D>;
-    __shared__ __attribute__((aligned(16))) uint16_t Ks[C::TILE];
-    const int qt = blockIdx.x, h = blockIdx.y;
+    __shared__ __attribute__((aligned(16))) uint16_t Ks[2][C::TILE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, hl = lane >> 5;
     const int Lq = a.Lq;
-    float *bins = a.part + (((size_t)h * a.n_qtiles + qt) * 8 + wave) * a.mass_bins;
-    for (int b = lane; b < a.mass_bins; b += 64) bins[b] = 0.f;
-
-    const int qrow = qt * BM + wave * 32 + l32;
-    const bool qok = qrow < Lq;
-    const uint16_t *Qh = (const uint16_t *)a.Q + (size_t)h * Lq * D;
-    bf16x8_t qf[C::KS];
-#pragma unroll
-    for (int kk = 0; kk < C::KS; ++kk) {
-        const u32x4 v = qok ? *(const u32x4 *)(Qh + (size_t)qrow * D + kk * 16 + hl * 8) : u32x4{0, 0, 0, 0};
-        qf[kk] = __builtin_bit_cast(bf16x8_t, v);
-    }
-    // rows past Lq contribute nothing: their bias is -inf
-    const float bias = qok ? -a.lse[(size_t)h * Lq + qrow] * 1.4426950408889634f : -__builtin_inff();
     const float c2 = a.scale_log2;
-
-    const int kvl = head_kvl(a, h);
-    const int Lk = kvl + Lq;
-    const uint16_t *Kc = (const uint16_t *)a.Kc + (size_t)h * a.slab * D;
-    const uint16_t *Kq = (const uint16_t *)a.K_cur + (size_t)h * Lq * D;
     // staging geometry: all 512 threads, rows r0 + RPP2*i
     constexpr int RPP2 = kThreads / C::CPR;
     constexpr int NV2 = BN / RPP2;
@@ -765,47 +764,118 @@ __global__ __launch_bounds__(kThreads) void attn_mass_kernel(AttnArgs a) {
     const uint32_t voff = (uint32_t)(r0 * D + c * 8) * 2u;
     const int wofs = r0 * C::RSE + c * 8;
     const int kbase = l32 * C::RSE + hl * 8;
-    const int vbase = 0;
 
-    f32x16_t o[C::MB];
-    f32x16_t s[2];
-    bf16x8_t pb[4];
-    const int T = (Lk + BN - 1) / BN;
-    for (int t = 0; t < T; ++t) {
-        const int j0 = t * BN;
+    // the units of this workgroup: T = bins of the entry's head
+    WorkList wl;
+    wl.T = lane < a.heads.n ? mass_bins_of(a, lane) : 0;   // (every head, in order)
+    {
+        long long v = (long long)a.n_qtiles * wl.T;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const long long u = __shfl_up(v, d, 64);
+            if (lane >= d) v += u;
+        }
+        wl.incl = (int64_t)v;
+    }
+    const Schedule sc = make_schedule(a, wl);
+    const int r = (blockIdx.x & 7) * (a.n_blocks >> 3) + (blockIdx.x >> 3);
+    if (r >= sc.G) return;
+    const int64_t end = sc.start(r + 1);
+    for (int64_t cur = sc.start(r); cur < end;) {
+        const ItemPos ip = locate(wl, cur);
+        const int h = ip.li, qt = ip.qt;
+        const int b0 = (int)(cur - ip.ibase);
+        const int b1 = (int)((end < ip.ibase + ip.T ? end : ip.ibase + ip.T) - ip.ibase);
+        cur = ip.ibase + b1;
+
+        const int qrow = qt * BM + wave * 32 + l32;
+        const bool qok = qrow < Lq;
+        const uint16_t *Qh = (const uint16_t *)a.Q + (size_t)h * Lq * D;
+        bf16x8_t qf[C::KS];
+#pragma unroll
+        for (int kk = 0; kk < C::KS; ++kk) {
+            const u32x4 v = qok ? *(const u32x4 *)(Qh + (size_t)qrow * D + kk * 16 + hl * 8) : u32x4{0, 0, 0, 0};
+            qf[kk] = __builtin_bit_cast(bf16x8_t, v);
+        }
+        // rows past Lq contribute nothing: their bias is -inf
+        const float bias = qok ? -a.lse[(size_t)h * Lq + qrow] * 1.4426950408889634f : -__builtin_inff();
+        const int kvl = head_kvl(a, h);
+        const int Lk = kvl + Lq;
+        const uint16_t *Kc = (const uint16_t *)a.Kc + (size_t)h * a.slab * D;
+        const uint16_t *Kq = (const uint16_t *)a.K_cur + (size_t)h * Lq * D;
+        float *bins = a.part + (((size_t)h * a.n_qtiles + qt) * 8 + wave) * a.mass_bins;
+
+        // tile positions: bin b, first key j; past the last bin the position is empty
+        struct Pos {
+            int b, j, hi;   // hi: end of the bin's keys
+        };
+        auto bin_at = [&](int b) { return Pos{b, b * a.mass_F, min((b + 1) * a.mass_F, Lk)}; };
+        auto next = [&](const Pos &p) {
+            return p.j + BN < p.hi ? Pos{p.b, p.j + BN, p.hi} : bin_at(p.b + 1);
+        };
         u32x4 stage[4];
-        load_tile<D, NV2>(Kc, Kq, j0, kvl, Lk, Lq, stage, voff, RPP2 * D * 2);
-        __syncthreads();  // the previous tile's reads are done
+        auto load = [&](const Pos &p) {
+            load_tile<D, NV2>(Kc, Kq, p.j, kvl, Lk, Lq, stage, voff, RPP2 * D * 2);
+        };
+        auto store = [&](uint16_t *t) {
 #pragma unroll
-        for (int i = 0; i < NV2; ++i) *(u32x4 *)(Ks + wofs + i * RPP2 * C::RSE) = stage[i];
+            for (int i = 0; i < NV2; ++i) *(u32x4 *)(t + wofs + i * RPP2 * C::RSE) = stage[i];
+        };
+        Pos p = bin_at(b0), p1 = next(p);
+        load(p);
+        store(Ks[0]);                       // (the previous item's last reads are behind its last barrier)
+        if (p1.b < b1) load(p1);
         __syncthreads();
-        mfma_block<D, false, true>(nullptr, Ks, vbase, kbase, pb, qf, o, s);
-        // keys of this lane: j0 + 32kb + 8(i/4) + 4hl + i%4
-        const int b_first = j0 / a.mass_F, b_last = (min(j0 + BN, Lk) - 1) / a.mass_F;
-        for (int b = b_first; b <= b_last; ++b) {
-            const int lo = b * a.mass_F, hi = min(lo + a.mass_F, Lk);
-            float v = 0.f;
+        float v0 = 0.f, v1 = 0.f;
+        for (int it = 0; p.b < b1; ++it) {
+            const Pos p2 = next(p1);
+            if (p1.b < b1) {
+                store(Ks[(it + 1) & 1]);    // last read before the barrier just passed
+                if (p2.b < b1) load(p2);
+            }
+            f32x16_t o[C::MB], s[2];
+            bf16x8_t pb[4];
+            mfma_block<D, false, true>(nullptr, Ks[it & 1], 0, kbase, pb, qf, o, s);
+            // keys of this lane: j + 32kb + 8(i/4) + 4hl + i%4
+            if (p.j + BN > p.hi) {
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int key = j0 + kb * 32 + 8 * (i >> 2) + 4 * hl + (i & 3);
-                    if (key >= lo && key < hi) v += __builtin_amdgcn_exp2f(fmaf(s[kb][i], c2, bias));
-                }
-            v = wave_sum_f(v);
-            if (lane == 0) bins[b] += v;
+                    for (int i = 0; i < 16; ++i)
+                        if (p.j + kb * 32 + 8 * (i >> 2) + 4 * hl + (i & 3) >= p.hi) s[kb][i] = -__builtin_inff();
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                v0 += __builtin_amdgcn_exp2f(fmaf(s[0][i], c2, bias));
+                v1 += __builtin_amdgcn_exp2f(fmaf(s[1][i], c2, bias));
+            }
+            if (p1.b != p.b) {
+                const float v = wave_sum_f(v0 + v1);
+                if (lane == 0) bins[p.b] = v;
+                v0 = v1 = 0.f;
+            }
+            __syncthreads();
+            p = p1;
+            p1 = p2;
         }
     }
 }
 
-template <int D>
+// mass[h][b]: the sum of the bin's n_qtiles * 8 wave sums (0 for a bin past the
+// head's keys).  One wave per bin: lane l adds rows l, l + 64, ... in order,
+// then a fixed butterfly.
 __global__ __launch_bounds__(256) void attn_mass_finalize_kernel(AttnArgs a) {
-    const int h = blockIdx.x;
-    for (int b = threadIdx.x; b < a.mass_bins; b += 256) {
+    const int h = blockIdx.y, lane = threadIdx.x & 63;
+    const int n = a.n_qtiles * 8, nb = mass_bins_of(a, h);
+    for (int b = blockIdx.x * 4 + (threadIdx.x >> 6); b < a.mass_bins; b += gridDim.x * 4) {
         float v = 0.f;
-        for (int k = 0; k < a.n_qtiles * 8; ++k) v += a.part[((size_t)h * a.n_qtiles * 8 + k) * a.mass_bins + b];
-        float *out = a.mass_out + (size_t)h * a.mass_bins + b;
-        *out = a.mass_acc ? *out + v : v;
+        if (b < nb)
+            for (int k = lane; k < n; k += 64) v += a.part[((size_t)h * n + k) * a.mass_bins + b];
+        v = wave_sum_f(v);
+        if (lane == 0) {
+            float *out = a.mass_out + (size_t)h * a.mass_bins + b;
+            *out = a.mass_acc ? *out + v : v;
+        }
     }
 }
 
@@ -833,14 +903,12 @@ hipError_t launch_attention_bf16(const AttnArgs &a, int head_dim, hipStream_t s)
 }
 
 hipError_t launch_attention_mass(const AttnArgs &a, int head_dim, hipStream_t s) {
-    const dim3 grid((unsigned)a.n_qtiles, (unsigned)a.n_heads);
-    if (head_dim == 128) {
-        hipLaunchKernelGGL(attn_mass_kernel<128>, grid, dim3(kThreads), 0, s, a);
-        hipLaunchKernelGGL(attn_mass_finalize_kernel<128>, dim3(a.n_heads), dim3(256), 0, s, a);
-    } else {
-        hipLaunchKernelGGL(attn_mass_kernel<64>, grid, dim3(kThreads), 0, s, a);
-        hipLaunchKernelGGL(attn_mass_finalize_kernel<64>, dim3(a.n_heads), dim3(256), 0, s, a);
-    }
+    if (head_dim == 128)
+        hipLaunchKernelGGL(attn_mass_kernel<128>, dim3(a.n_blocks), dim3(kThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(attn_mass_kernel<64>, dim3(a.n_blocks), dim3(kThreads), 0, s, a);
+    const unsigned bx = (unsigned)((a.mass_bins + 3) / 4);
+    hipLaunchKernelGGL(attn_mass_finalize_kernel, dim3(bx < 64 ? bx : 64, (unsigned)a.n_heads), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
