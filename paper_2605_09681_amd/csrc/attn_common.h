@@ -53,6 +53,14 @@ struct Schedule {
     __device__ __forceinline__ int owner(int64_t x) const { return (int)(((x + 1) * G - 1) / total); }
 };
 
+// Slot of the first part of the item whose tiles start at ibase: the item is its
+// first owner's last segment unless that workgroup's range starts with it, and
+// the first segment of every later owner.
+__device__ __forceinline__ int first_slot(const Schedule &sc, int64_t ibase) {
+    const int b0 = sc.owner(ibase);
+    return sc.start(b0) == ibase ? 2 * b0 : 2 * b0 + 1;
+}
+
 // The launch's work list as one wave sees it: lane l < heads.n holds the key
 // tile count T of list entry l and the inclusive prefix sum of n_qtiles * T
 // over entries 0..l; lanes past the list repeat the total.  One vector load of
@@ -121,6 +129,26 @@ __device__ __forceinline__ Schedule make_schedule(const AttnArgs &a, const WorkL
     sc.total = total;
     sc.G = (int)(total < a.n_blocks ? total : a.n_blocks);
     return sc;
+}
+
+// Whole parts instead of equal ranges where the chip has workgroups to spare:
+// every item is cut into `parts` (one workgroup each, at most one per tile), so
+// no workgroup computes the ends of two items.  A segment costs about
+// kSegmentTiles tiles beside its own (the first loads, the first tile's row
+// maxima, the epilogue), and an equal range shorter than an item usually holds
+// two: whole parts win where the longest one is within a segment's cost of an
+// equal range.  0: equal ranges.  (16 heads of 64, 666 query rows, 32 and 44 key
+// tiles per query tile, 48 items: the layer step takes 47.4 us, 53.3 with equal
+// ranges.)
+constexpr int kSegmentTiles = 4;
+__device__ __forceinline__ int whole_parts(const AttnArgs &a, const WorkList &wl, const Schedule &sc) {
+    const int parts = a.n_blocks / a.n_items;
+    if (parts < 2 || sc.total == 0) return 0;
+    int longest = wl.T;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) longest = max(longest, __shfl_xor(longest, d, 64));
+    longest = __builtin_amdgcn_readfirstlane((longest + parts - 1) / parts);
+    return longest <= (int)(sc.total / sc.G) + kSegmentTiles ? parts : 0;
 }
 
 // Partial result of one part of an item, in a slot of BM*(D/2 + 2) floats:

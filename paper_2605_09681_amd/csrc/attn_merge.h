@@ -13,9 +13,9 @@
 namespace fkv {
 namespace attn {
 
-// Combines the parts of a cut item (list entry li, query tile qt; first tile
-// ibase of the concatenated sequence, T tiles), for the 32 rows of wave block
-// w.  With part maxima m_j, sums l_j and normalised outputs o_j of a row,
+// Combines the parts of a cut item (list entry li, query tile qt), computed by
+// workgroups b0 .. b1: the first one's part is in slot s0, every later one's in
+// the first of its two slots.  For the 32 rows of wave block w.  With part maxima m_j, sums l_j and normalised outputs o_j of a row,
 //   M = max_j m_j,  w_j = 2^(m_j - M) l_j,  L = sum_j w_j,  O = sum_j w_j o_j / L,
 // and lse = ln 2 * M + ln L, the parts taken in schedule order.  Thread t of
 // the NT that share the block handles row t % 32 and the block's uint2
@@ -24,17 +24,12 @@ namespace attn {
 // workgroups, so they are read with device-scope loads; every other part is
 // complete when its workgroup arrives, so nothing waits.
 template <int D, int NT>
-__device__ __forceinline__ void merge_rows(const AttnArgs &a, const Schedule &sc, int li, int qt, int64_t ibase,
-                                           int T, int w, int t) {
+__device__ __forceinline__ void merge_rows(const AttnArgs &a, int b0, int b1, int s0, int li, int qt, int w, int t) {
     constexpr int MB = D / 32;             // 32-row blocks of O^T
     constexpr int kML = BM * D / 2;        // float offset of m within a slot
     constexpr int kVecs = MB * 4 * 64;     // uint2s (4 values) of one wave block's accumulators
     constexpr int kPer = kVecs / NT;
     const int h = a.heads.head[li];
-    const int b0 = sc.owner(ibase), b1 = sc.owner(ibase + T - 1);
-    // the item is b0's last segment unless b0's range starts with it, and the
-    // first segment of every later workgroup up to b1
-    const int s0 = sc.start(b0) == ibase ? 2 * b0 : 2 * b0 + 1;
     const int r = t & 31, row = w * 32 + r;
     const int qrow = qt * BM + row;
     float M = -__builtin_inff(), L = 0.f;

@@ -8,15 +8,14 @@
 // the history/chunk boundary.  The PAGED instantiation attends heads in place:
 // their retained history -- the kept frames of Eq. 2 for static heads, the
 // kept segments of Eq. 3 for dynamic heads -- is read straight from the
-// slot-permuted cache through a per-head page table (load_tile_paged), with no
+// slot-permuted cache through a per-head page table (paged_tile), with no
 // compressed copy.
 //
-// Workgroup = 8 waves = 256 query rows of one head (32 per wave), in two
-// groups of four waves; one workgroup fills a CU.  Keys are processed in tiles
-// of 64.  Per wave and tile, with v_mfma_f32_32x32x16_bf16:
+// Workgroup = 8 waves = 256 query rows of one head (32 per wave); one workgroup
+// fills a CU.  Keys are processed in tiles of 64.  Per wave and tile, with v_mfma_f32_32x32x16_bf16:
 //   S^T = K . Q^T   (A = K rows from LDS, B = the wave's Q rows, held in VGPRs),
 //                   2 x (d/16) MFMAs;
-//   online softmax in fp32 (exp2 with the scale folded into log2 units; the
+//   softmax in fp32 (exp2 with the scale folded into log2 units; the
 //                   row sum adds the bf16-rounded probabilities with v_dot2);
 //   O^T += V^T . P^T (A = rows of a V^T tile in LDS, B = P taken straight from
 //                    the S^T accumulators, rounded to bf16), 4 x (d/32) MFMAs.
@@ -25,25 +24,42 @@
 // lane holds 16 keys of its query, which are exactly the 8-element k-slices the
 // B operand of the value product takes (any consistent permutation of the
 // contraction index is allowed; the V^T tile is stored with the same
-// permutation).  Row maxima need one cross-lane exchange (lanes l and l^32
-// share a query).  Both operands are read from LDS with 16-byte reads; V is
+// permutation).  Both operands are read from LDS with 16-byte reads; V is
 // transposed on its way into LDS (measured faster than the LDS transpose
 // reads).
 //
-// The two wave groups run the same loop one phase apart (see attn_segment), so
-// on every SIMD one wave's softmax overlaps the other wave's MFMA block -- VALU
-// and MFMA work of two waves overlap well, that of one wave much less.  The
-// running max only moves when a tile's max exceeds it by more than 8 (log2
-// units): probabilities stay below 2^8 and the accumulator rescale is skipped
-// for most tiles; the final normalisation is exact either way.
+// Per 64-key tile a wave issues 32 products (D = 128), 32 operand reads and the
+// tile's 32 exponentials with their scaling, rounding and sums.  The loop
+// (attn_segment) interleaves them in one pinned order: products of one tile's
+// scores and the previous one's values alternate, a few VALU instructions behind
+// each, so the exponentials of a key block run while 16 other products do, and
+// nothing in a wave waits for a row maximum: the exponentials' reference is the
+// row maximum of the segment's first tile.  Probabilities may then exceed one,
+// in bf16 and fp32 by 2^100 and more without loss (their relative rounding is
+// the same); a segment in which a sum passes 2^100 or an output is not finite is
+// computed again with a running maximum (it moves where a tile's exceeds it by
+// more than 8 in log2 units).
+// Bound: at 1080P the clock, which the power of the products holds at 1.75-1.85
+// GHz (a 8192^3 library product reaches 1.2 PFLOP/s on this card, a bare loop of
+// these products, reads and exponentials 1.44), and 66% of the cycles issue a
+// product (60% before, when the softmax of one wave group ran beside the
+// products of the other: its row maximum, its scalar page arithmetic of some 70
+// instructions per tile and its wait for the second part of a straddling tile
+// were in the way).  1080P layer step 12.60 -> 12.08 ms, 480P 528 -> 508 us, with
+// quarter-frame segments, where every sixth tile straddles, 452 -> 425 us.
+// Measured beside it (480P step, same box): the wave groups half an iteration
+// apart 544 against 527 us; loads issued a whole run of scalar branches after the
+// tile's last product 527 against 508 us (a run of full tiles now costs a scalar
+// add); the exponentials in the second half of an iteration 572 us.
 //
 // Global K/V rows come in through buffer loads whose per-lane offsets are loop
 // invariant; rows past the end of a source fall outside the buffer's range and
-// read as zero (the straddling tile merges both sources that way).
+// read as zero.
 //
 // Schedules: a work item is (entry of the launch's head list, query tile);
 // one workgroup per item, or the balanced schedule (attn_common.h) that splits
-// the key tiles of all items evenly over one workgroup per CU; the parts of a
+// the key tiles of all items evenly, or every item in as many parts as there are
+// workgroups to spare, over one workgroup per CU; the parts of a
 // split item are merged by the workgroup that completes the last of them
 // (merge_rows).  Heads with longer caches make the per-item
 // schedule uneven (at 480P a dynamic head has 342 key tiles per query tile, a
@@ -62,8 +78,9 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kThreads = 512;      // 8 waves: two groups of 4
-constexpr int kGroupThreads = 256; // one group stages a whole K or V tile
+constexpr int kThreads = 512;      // 8 waves
+constexpr int kBufs = 4;           // K and V^T tiles in LDS
+constexpr float kSumLimit = 0x1p100f; // a larger sum of probabilities redoes the segment with a running max
 constexpr float kRescaleSlack = 8.f;  // log2 units the running max may lag behind
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // raw 32-bit buffer, range checked
 constexpr bf16x2_t kOnes2 = {(__bf16)1.f, (__bf16)1.f};
@@ -73,22 +90,23 @@ struct Cfg {
     static constexpr int RSE = D + 8;           // K row stride in LDS (16-byte pad), elements
     static constexpr int TRSE = BN + 8;         // V^T row stride in LDS (16-byte pad), elements
     static constexpr int CPR = D / 8;           // 16-byte chunks per row
-    static constexpr int RPP = kGroupThreads / CPR;  // rows one pass of a 256-thread group covers
-    static constexpr int NV = BN / RPP;              // 16-byte vectors per thread per staged tile
+    static constexpr int RPP = kThreads / CPR;  // rows one pass of the workgroup covers
+    static constexpr int NV = BN / RPP;         // 16-byte vectors per thread per staged K tile
+    static constexpr int VW = D / 64;           // 4-byte words (2 dims) per thread and key of a staged V tile
     static constexpr int KS = D / 16;           // k-steps of S^T = K Q^T
     static constexpr int MB = D / 32;           // 32-row blocks of O^T
     static constexpr int TILE = BN * RSE;       // elements per K tile
     static constexpr int VTILE = D * TRSE;      // elements per V^T tile
-    static constexpr int VUNITS = (BN / 4) * CPR;  // (4 keys x 8 dims) units of a V tile
     static_assert(NV >= 1 && BN % RPP == 0, "tile shape");
+    static_assert((BN / 4) * (D / (2 * VW)) == kThreads, "one V unit (4 keys x 2 VW dims) per thread");
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, kRsrcWord3);
 }
 
-__device__ __forceinline__ u32x4 bload(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+__device__ __forceinline__ u32x4 bload(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff = 0) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
 }
 
 // Rows of the key tile starting at j0 of [hist (kvl rows); chunk (Lq rows)] into
@@ -176,11 +194,6 @@ __device__ __forceinline__ int kept_piece(uint32_t tab, int y) {
     return (int)((uint32_t)__builtin_amdgcn_readlane((int)tab, y & 63) >> (8 * (y >> 6))) & 255;
 }
 
-// The same for a head read in place from the cache (paged): history row p is
-// row p mod P of kept piece y = p / P, at cache row kept_piece(tab, y) * P.
-// With P >= 64 a tile touches at most two kept pieces and the chunk; each part
-// has its own range-checked buffer and the three loads are OR-ed, every row
-// outside a part reading as zero.
 // j0 / P for 0 <= j0 < 2^31 with the launch's 64-bit reciprocal M = floor(2^64 / P) + 1
 // (= magic_hi * 2^32 + magic_lo): floor(j0 * M / 2^64) exactly, since j0 * M / 2^64
 // exceeds j0 / P by less than 2^-33 < 1 / P.  A few scalar multiplies instead of
@@ -188,39 +201,6 @@ __device__ __forceinline__ int kept_piece(uint32_t tab, int y) {
 __device__ __forceinline__ int div_piece(const AttnArgs &a, int j0) {
     const uint64_t p = (uint64_t)(uint32_t)j0 * a.pg_magic_hi + __umulhi((uint32_t)j0, a.pg_magic_lo);
     return (int)(p >> 32);
-}
-
-template <int D, int N>
-__device__ __forceinline__ void load_tile_paged(const AttnArgs &a, const uint16_t *hist, uint32_t tab, int P,
-                                                const uint16_t *chunk, int j0, int kvl, int Lk, int Lq,
-                                                u32x4 *dst, uint32_t off0, uint32_t step) {
-    if (j0 >= kvl) {
-        const auto r = rsrc(chunk + (size_t)(j0 - kvl) * D, (uint32_t)(Lk - j0) * D * 2);
-#pragma unroll
-        for (int i = 0; i < N; ++i) dst[i] = bload(r, off0 + i * step);
-        return;
-    }
-    auto piece = [&](int y) { return hist + (size_t)kept_piece(tab, y) * P * D; };
-    const int y0 = div_piece(a, j0), r0 = j0 - y0 * P;
-    const int na = min(min(P - r0, kvl - j0), BN);            // rows of kept piece y0
-    const auto ra = rsrc(piece(y0) + (size_t)r0 * D, (uint32_t)na * D * 2);
-    if (na == BN) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) dst[i] = bload(ra, off0 + i * step);
-        return;
-    }
-    // the rest of the tile: the next kept piece while history lasts, then the chunk
-    const int nb = j0 + na < kvl ? min(BN - na, kvl - (j0 + na)) : 0;
-    const int nc = j0 + na + nb >= kvl ? min(BN - na - nb, Lq) : 0;
-    const auto rb = rsrc(nb > 0 ? piece(y0 + 1) : hist, (uint32_t)nb * D * 2);
-    const auto rc = rsrc(chunk, (uint32_t)nc * D * 2);
-    const uint32_t sb = (uint32_t)na * D * 2, sc = (uint32_t)(na + nb) * D * 2;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const uint32_t o = off0 + i * step;
-        // rows before a part's start wrap to huge offsets: out of range, read 0
-        dst[i] = bload(ra, o) | bload(rb, o - sb) | bload(rc, o - sc);
-    }
 }
 
 // Position of a key tile of a head read in place: its first key j0 and, while
@@ -235,92 +215,94 @@ struct PageCursor {
     uint32_t off;  // element offset of history row j0 in the head's cache (j0 < kvl)
 };
 
-// The tile at `c` (as load_tile_paged).  The history length kvl is a whole
-// number of pieces, so a tile starting in piece y holds min(P - r, BN) rows of
-// it, then the next piece's rows while history lasts, then the chunk's.
-template <int D, int N>
-__device__ __forceinline__ void load_tile_cursor(const uint16_t *hist, uint32_t tab, int P, const PageCursor &c,
-                                                 const uint16_t *chunk, int kvl, int Lk, int Lq, u32x4 *dst,
-                                                 uint32_t off0, uint32_t step) {
+// A 64-key tile's rows: part `a`, and where the tile crosses from one source to
+// the next (a kept piece to another, or the history to the chunk) part `b`,
+// whose first row is `shift` bytes into the tile.  Rows past the last part fall
+// outside its buffer's range and read as zero.
+struct TileSrc {
+    __amdgpu_buffer_rsrc_t a, b;
+    uint32_t shift;
+    bool two;
+};
+
+// Read in place: the history length kvl is a whole number of pieces of P >= 64
+// rows, so a tile starting in piece y holds min(P - r, BN) rows of it, then the
+// next piece's rows while history lasts, then the chunk's.
+template <int D>
+__device__ __forceinline__ TileSrc paged_tile(const uint16_t *hist, uint32_t tab, int P, const PageCursor &c,
+                                              const uint16_t *chunk, int kvl, int Lk, int Lq) {
     if (c.j0 >= kvl) {
         const auto r = rsrc(chunk + (size_t)(c.j0 - kvl) * D, (uint32_t)(Lk - c.j0) * D * 2);
-#pragma unroll
-        for (int i = 0; i < N; ++i) dst[i] = bload(r, off0 + i * step);
-        return;
+        return TileSrc{r, r, 0u, false};
     }
     const int na = min(P - c.r, BN);
-    const auto ra = rsrc(hist + c.off, (uint32_t)na * D * 2);
-    if (na == BN) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) dst[i] = bload(ra, off0 + i * step);
-        return;
-    }
     const bool more = c.j0 + na < kvl;  // another kept piece follows, else the chunk
-    const auto rb = rsrc(more ? hist + (size_t)kept_piece(tab, c.y + 1) * P * D : chunk,
-                         (uint32_t)(more ? BN - na : min(BN - na, Lq)) * D * 2);
-    const uint32_t sb = (uint32_t)na * D * 2;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const uint32_t o = off0 + i * step;
-        // rows before the second part's start wrap to huge offsets: out of range, read 0
-        dst[i] = bload(ra, o) | bload(rb, o - sb);
-    }
+    const auto ra = rsrc(hist + c.off, (uint32_t)na * D * 2);
+    if (na == BN) return TileSrc{ra, ra, 0u, false};
+    return TileSrc{ra,
+                   rsrc(more ? hist + (size_t)kept_piece(tab, c.y + 1) * P * D : chunk,
+                        (uint32_t)(more ? BN - na : min(BN - na, Lq)) * D * 2),
+                   (uint32_t)na * D * 2, true};
 }
 
-// One MFMA block of a wave: optionally O^T += V^T P^T for one key tile (4 x MB
-// products, accumulators o[mb] cycled so consecutive products are independent),
-// then optionally S^T = K Q^T for the next tile (KS x 2 products, the two
-// accumulators interleaved).  The A operand of every product comes from LDS;
-// its reads are issued kPrefetch products ahead so their latency overlaps the
-// preceding products.
-constexpr int kPrefetch = 4;
-
-template <int D, bool PV, bool QK>
-__device__ __forceinline__ void mfma_block(const uint16_t *vs, const uint16_t *ks, int vbase, int kbase,
-                                           const bf16x8_t (&pb)[4], const bf16x8_t (&qf)[D / 16],
-                                           f32x16_t (&o)[D / 32], f32x16_t (&s)[2]) {
-    using C = Cfg<D>;
-    constexpr int NPV = PV ? 4 * C::MB : 0;
-    constexpr int NQK = QK ? 2 * C::KS : 0;
-    constexpr int NSTEP = NPV + NQK;
-    // Step order: the value products (accumulators o[mb] cycled) then the score
-    // products (accumulators s[0], s[1] alternating).
-    auto is_pv = [&](int st) { return st < NPV; };
-    auto index = [&](int st) { return st < NPV ? st : st - NPV; };
-    auto read_a = [&](int st) -> bf16x8_t {
-        const int i = index(st);
-        if (is_pv(st)) {
-            const int t = i / C::MB, mb = i % C::MB;
-            return __builtin_bit_cast(bf16x8_t, *(const u32x4 *)(vs + vbase + (32 * mb) * C::TRSE + 16 * t));
-        }
-        const int kk = i >> 1, kb = i & 1;
-        return __builtin_bit_cast(bf16x8_t, *(const u32x4 *)(ks + kbase + kb * 32 * C::RSE + kk * 16));
-    };
-    if (QK) {
-        s[0] = f32x16_t{};
-        s[1] = f32x16_t{};
+// Over a compact copy: [hist (kvl rows); chunk (Lq rows)].
+template <int D>
+__device__ __forceinline__ TileSrc compact_tile(const uint16_t *hist, const uint16_t *chunk, int j0, int kvl, int Lk,
+                                                int Lq) {
+    if (j0 >= kvl) {
+        const auto r = rsrc(chunk + (size_t)(j0 - kvl) * D, (uint32_t)(Lk - j0) * D * 2);
+        return TileSrc{r, r, 0u, false};
     }
+    const int na = min(kvl - j0, BN);
+    const auto ra = rsrc(hist + (size_t)j0 * D, (uint32_t)na * D * 2);
+    if (na == BN) return TileSrc{ra, ra, 0u, false};
+    return TileSrc{ra, rsrc(chunk, (uint32_t)min(BN - na, Lq) * D * 2), (uint32_t)na * D * 2, true};
+}
+
+template <int W>
+struct Words;
+template <>
+struct Words<1> {
+    uint32_t w[1];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff) {
+        w[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
+    }
+};
+template <>
+struct Words<2> {
+    uint32_t w[2];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
+        w[0] = (uint32_t)v[0];
+        w[1] = (uint32_t)v[1];
+    }
+};
+
+constexpr int kPrefetch = 4;   // operand reads in flight ahead of the product that takes them
+
+// S^T = K Q^T for one key tile in LDS (KS products per key block), the operand
+// reads kPrefetch products ahead.
+template <int D>
+__device__ __forceinline__ void score_block(const uint16_t *ks, int kbase, const bf16x8_t (&qf)[D / 16],
+                                            f32x16_t (&s)[2]) {
+    using C = Cfg<D>;
+    constexpr int NSTEP = 2 * C::KS;
+    auto read_a = [&](int i) {
+        return __builtin_bit_cast(bf16x8_t, *(const u32x4 *)(ks + kbase + (i & 1) * 32 * C::RSE + (i >> 1) * 16));
+    };
+    s[0] = f32x16_t{};
+    s[1] = f32x16_t{};
     bf16x8_t fr[kPrefetch];
 #pragma unroll
-    for (int i = 0; i < kPrefetch; ++i)
-        if (i < NSTEP) fr[i] = read_a(i);
+    for (int i = 0; i < kPrefetch; ++i) fr[i] = read_a(i);
 #pragma unroll
     for (int st = 0; st < NSTEP; ++st) {
-        const bf16x8_t a = fr[st % kPrefetch];
+        const bf16x8_t x = fr[st % kPrefetch];
         if (st + kPrefetch < NSTEP) fr[st % kPrefetch] = read_a(st + kPrefetch);
-        const int i = index(st);
-        if (is_pv(st)) {
-            const int t = i / C::MB, mb = i % C::MB;
-            o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[t], o[mb], 0, 0, 0);
-        } else {
-            const int kk = i >> 1, kb = i & 1;
-            s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], s[kb], 0, 0, 0);
-        }
+        s[st & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, qf[st >> 1], s[st & 1], 0, 0, 0);
     }
-    // Keep the operand reads kPrefetch products ahead: kPrefetch LDS reads,
-    // then alternate one MFMA and one LDS read.
 #pragma unroll
-    for (int i = 0; i < kPrefetch && i < NSTEP; ++i) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    for (int i = 0; i < kPrefetch; ++i) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
 #pragma unroll
     for (int st = 0; st < NSTEP; ++st) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -335,13 +317,11 @@ __device__ __forceinline__ void mfma_block(const uint16_t *vs, const uint16_t *k
 // partial result goes to the slot.  Uses every thread of the workgroup and
 // leaves no LDS read pending.
 template <int D, bool PAGED>
-__device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t (&Ks)[2][Cfg<D>::TILE],
-                                             uint16_t (&Vs)[2][Cfg<D>::VTILE], int li, int qt, int t0,
-                                             int t1, int rot, float *slot) {
+__device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, uint16_t *Vs, uint32_t *redo, int li,
+                                             int qt, int t0, int t1, int rot, float *slot) {
     using C = Cfg<D>;
     const int h = a.heads.head[li];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int grp = wave >> 2;  // 0: leads by half a tile, 1: trails
     const int l32 = lane & 31, hl = lane >> 5;
     const int Lq = a.Lq;
     const int n = t1 - t0;       // >= 1
@@ -368,54 +348,35 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t (&Ks)[2
     const uint16_t *Vq = (const uint16_t *)a.V_cur + (size_t)h * Lq * D;
     const uint32_t ktab = PAGED ? kept_piece_table(a, li, kvl, lane) : 0u;
 
-    // Loop-invariant per-thread load geometry within the thread's group of 256:
-    // rows r0 + RPP*i, chunk c (group 0 stages K tiles, group 1 V tiles).
-    const int gtid = tid & 255;
-    const int c = gtid % C::CPR, r0 = gtid / C::CPR;
+    // Loop-invariant per-thread staging geometry.  K: rows r0 + RPP*i, 16-byte
+    // chunk c.  V: keys 4*vq .. 4*vq+3 of the tile, dims 2*VW*vc .. +2*VW, stored
+    // transposed: row d of the V^T tile holds the tile's 64 keys, and within each
+    // 16-key group the key quads sit in the order 0, 2, 1, 3 so that the 8 keys a
+    // lane feeds to the value product (16t + 4hl + 0..3 and 16t + 8 + 4hl + 0..3)
+    // are contiguous.
+    const int c = tid % C::CPR, r0 = tid / C::CPR;
     const uint32_t voff = (uint32_t)(r0 * D + c * 8) * 2u;    // + i*RPP*D*2 bytes
     const int wofs = r0 * C::RSE + c * 8;                      // + i*RPP*RSE elements
-    // V staging unit of this thread: keys 4*vq .. 4*vq+3 of the tile, dims 8*vc .. 8*vc+7.
-    const int vq = gtid % (BN / 4), vc = gtid / (BN / 4);
-    const uint32_t voffv = (uint32_t)(4 * vq * D + vc * 8) * 2u;  // + r*D*2 bytes
+    const int vq = tid % (BN / 4), vc = tid / (BN / 4);
+    const uint32_t voffv = (uint32_t)(4 * vq * D + vc * 2 * C::VW) * 2u;  // + r*D*2 bytes
+    const int vofs = 2 * C::VW * vc * C::TRSE + 16 * (vq >> 2) + 4 * (((vq & 1) << 1) | ((vq >> 1) & 1));
 
-    // first key of the segment's tile j
+    // The segment's key tiles: kt0, kt0 + 1, ... (mod T); where the keys end inside
+    // tile T - 1 and it is one of them, it comes first (the first tile's row maxima
+    // are taken, with the keys past Lk masked); the others are full ones.
     const int T = (Lk + BN - 1) / BN;
     const int kt0 = (t0 + rot) % T;
-    auto tile0 = [&](int j) {
-        const int k = kt0 + j;
-        return (k >= T ? k - T : k) * BN;
-    };
-    auto load_k = [&](int j0, u32x4 (&dst)[4]) {
-        if (PAGED)
-            load_tile_paged<D, C::NV>(a, Kc, ktab, a.pg_P, Kq, j0, kvl, Lk, Lq, dst, voff, C::RPP * D * 2);
-        else
-            load_tile<D, C::NV>(Kc, Kq, j0, kvl, Lk, Lq, dst, voff, C::RPP * D * 2);
-    };
-    auto load_v = [&](int j0, u32x4 (&dst)[4]) {
-        if (gtid < C::VUNITS) {
-            if (PAGED)
-                load_tile_paged<D, 4>(a, Vc, ktab, a.pg_P, Vq, j0, kvl, Lk, Lq, dst, voffv, D * 2);
-            else
-                load_tile<D, 4>(Vc, Vq, j0, kvl, Lk, Lq, dst, voffv, D * 2);
-        }
-    };
-    // In the tile loop each group loads tiles of consecutive positions (group 0
-    // V(it + 1), group 1 K(it + 3)); read in place, it follows them with a
-    // cursor instead of dividing every tile's first key by the piece length.
+    const bool ragged = Lk % BN != 0 && T - 1 - kt0 < n;
+    const int Tw = Lk / BN;             // the full tiles, which the order wraps over
     const int P = PAGED ? a.pg_P : 0;
     auto piece_off = [&](int y, int r) { return (uint32_t)(kept_piece(ktab, y) * P + r) * (uint32_t)D; };
-    auto cursor_at = [&](int j) {
-        const int j0 = tile0(j);
-        const int y = j0 < kvl ? div_piece(a, j0) : 0;
-        return PageCursor{j0, y, j0 - y * P, j0 < kvl ? piece_off(y, j0 - y * P) : 0u};
-    };
-    // next tile of the rotated order: inside a piece the offset moves on by a
-    // tile; the page table is read again only where a piece ends
+    // the next tile of the rotated order: read in place, the offset moves on by a
+    // tile inside a piece, and the page table is read where a piece ends
     auto advance = [&](PageCursor &cu) {
         cu.j0 += BN;
-        if (cu.j0 >= T * BN) {          // the rotated order wraps to the first tile
-            cu = PageCursor{0, 0, 0, kvl > 0 ? piece_off(0, 0) : 0u};
-        } else {
+        if (cu.j0 >= Tw * BN) {         // the order wraps to the first tile
+            cu = PageCursor{0, 0, 0, PAGED && kvl > 0 ? piece_off(0, 0) : 0u};
+        } else if (PAGED) {
             cu.r += BN;
             cu.off += BN * D;
             if (cu.r >= P) {
@@ -425,29 +386,91 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t (&Ks)[2
             }
         }
     };
-    auto store_k = [&](uint16_t *tile, const u32x4 (&src)[4]) {
-#pragma unroll
-        for (int i = 0; i < C::NV; ++i) *(u32x4 *)(tile + wofs + i * C::RPP * C::RSE) = src[i];
+
+    u32x4 kst[C::NV];
+    Words<C::VW> vst[4];
+    // Sources of the next tile's loads.  Full tiles that follow one another in one
+    // source (a piece, the compact history, the chunk) are a run: `left` more of them
+    // at soff, for which a tile's loads take a scalar add.  Any other tile is a run of
+    // one, of up to two parts.
+    __amdgpu_buffer_rsrc_t krun = rsrc(Kq, 0), vrun = krun, k2 = krun, v2 = krun;
+    uint32_t soff = 0, shift = 0;
+    int left = 0;
+    bool two = false;
+    auto one_tile = [&](const PageCursor &cu) {
+        const TileSrc k = PAGED ? paged_tile<D>(Kc, ktab, P, cu, Kq, kvl, Lk, Lq)
+                                : compact_tile<D>(Kc, Kq, cu.j0, kvl, Lk, Lq);
+        const TileSrc v = PAGED ? paged_tile<D>(Vc, ktab, P, cu, Vq, kvl, Lk, Lq)
+                                : compact_tile<D>(Vc, Vq, cu.j0, kvl, Lk, Lq);
+        krun = k.a;
+        vrun = v.a;
+        k2 = k.b;
+        v2 = v.b;
+        shift = k.shift;
+        two = k.two;
+        soff = 0;
+        left = 1;
     };
-    // V^T tile: row d holds the tile's 64 keys; within each 16-key group the key
-    // quads are stored in the order 0, 2, 1, 3 so that the 8 keys a lane feeds to
-    // the value product (16t + 4hl + 0..3 and 16t + 8 + 4hl + 0..3) are contiguous.
-    auto store_vt = [&](uint16_t *vt, const u32x4 (&src)[4]) {
-        if (gtid < C::VUNITS) {
-            const int qi = vq & 3;
-            const int col = 16 * (vq >> 2) + 4 * (((qi & 1) << 1) | (qi >> 1));
-            uint16_t *dst = vt + (8 * vc) * C::TRSE + col;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                // dims 8vc+2e (low halves) and 8vc+2e+1 (high halves) of the 4 keys
-                const uint2 lo = make_uint2((src[0][e] & 0xffffu) | (src[1][e] << 16),
-                                            (src[2][e] & 0xffffu) | (src[3][e] << 16));
-                const uint2 hi = make_uint2((src[0][e] >> 16) | (src[1][e] & 0xffff0000u),
-                                            (src[2][e] >> 16) | (src[3][e] & 0xffff0000u));
-                *(uint2 *)(dst + (2 * e) * C::TRSE) = lo;
-                *(uint2 *)(dst + (2 * e + 1) * C::TRSE) = hi;
-            }
+    // the run that starts at cu, and cu past it
+    auto next_run = [&](PageCursor &cu) {
+        const int end = Tw * BN;
+        const bool hist = cu.j0 < kvl;
+        const int lim = !hist ? end : min(end, PAGED ? cu.j0 + P - cu.r : kvl);
+        left = (lim - cu.j0) / BN;
+        if (PAGED && hist) left = min(left, (kvl - cu.j0 + BN - 1) / BN);
+        left = min(left, 1 << 16);    // (soff stays below 2^31)
+        if (left > 0) {
+            const size_t off = hist && PAGED ? (size_t)cu.off : (size_t)(hist ? cu.j0 : cu.j0 - kvl) * D;
+            krun = rsrc((hist ? Kc : Kq) + off, (uint32_t)left * (BN * D * 2));
+            vrun = rsrc((hist ? Vc : Vq) + off, (uint32_t)left * (BN * D * 2));
+            soff = 0;
+            const int m = left - 1;   // (advance adds the last one)
+            cu.j0 += m * BN;
+            cu.r += m * BN;
+            cu.off += (uint32_t)(m * BN * D);
+        } else {
+            one_tile(cu);
         }
+        advance(cu);
+    };
+    // one tile of the run into registers
+    auto load = [&]() {
+        if (!two) {
+#pragma unroll
+            for (int i = 0; i < C::NV; ++i) kst[i] = bload(krun, voff + i * (C::RPP * D * 2), soff);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vst[r].load(vrun, voffv + r * (D * 2), soff);
+        } else {
+            // each lane from the part that holds its row: no load waits for another
+#pragma unroll
+            for (int i = 0; i < C::NV; ++i) {
+                const uint32_t o = voff + i * (C::RPP * D * 2);
+                if (o < shift) kst[i] = bload(krun, o, 0);
+                else kst[i] = bload(k2, o - shift, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t o = voffv + r * (D * 2);
+                if (o < shift) vst[r].load(vrun, o, 0);
+                else vst[r].load(v2, o - shift, 0);
+            }
+            two = false;
+        }
+        soff += BN * D * 2;
+        --left;
+    };
+    constexpr int kStores = C::NV + 2 * C::VW;
+    // store x of the staged tile: the K vectors, then the V^T rows (4 keys each)
+    auto store = [&](int x, int b, const u32x4 (&kst)[C::NV], const Words<C::VW> (&vst)[4]) {
+        if (x < C::NV) {
+            *(u32x4 *)(Ks + b * C::TILE + wofs + x * C::RPP * C::RSE) = kst[x];
+            return;
+        }
+        const int e = x - C::NV, j = e >> 1;
+        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;   // high or low halves
+        *(uint2 *)(Vs + b * C::VTILE + vofs + e * C::TRSE) =
+            make_uint2(__builtin_amdgcn_perm(vst[1].w[j], vst[0].w[j], sel),
+                       __builtin_amdgcn_perm(vst[3].w[j], vst[2].w[j], sel));
     };
 
     // LDS read bases of the MFMA operands.
@@ -457,172 +480,271 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t (&Ks)[2
     // permuted V^T tile.
     const int vbase = l32 * C::TRSE + 8 * hl;
 
+    // Steps of iteration `it`, in four runs of products:
+    //   A  score products of key block 0 of tile it        (KS)
+    //   B  value products of key block 1 of tile it - 1    (2 MB: key group t, then dim block)
+    //   C  score products of key block 1 of tile it        (KS)
+    //   D  value products of key block 0 of tile it        (2 MB)
+    // so the exponentials of a key block have two runs of other products between
+    // its scores and its value products.  Operand A of step x (x >= NSTEP: the
+    // next iteration's run A).
+    constexpr int xB = C::KS, xC = xB + 2 * C::MB, xD = xC + C::KS, NSTEP = xD + 2 * C::MB;
+    static_assert(NSTEP % kPrefetch == 0 && kPrefetch <= C::KS, "operand ring");
+    auto buf = [](int tile) { return tile & (kBufs - 1); };
+    auto read_a = [&](int x, int it) -> bf16x8_t {
+        const bool score = x < xB || (x >= xC && x < xD) || x >= NSTEP;
+        if (score) {
+            const int kb = x >= xC && x < xD, kk = x >= NSTEP ? x - NSTEP : kb ? x - xC : x;
+            return __builtin_bit_cast(bf16x8_t, *(const u32x4 *)(Ks + buf(x >= NSTEP ? it + 1 : it) * C::TILE + kbase +
+                                                                kb * 32 * C::RSE + kk * 16));
+        }
+        const int y = x >= xD ? x - xD : x - xB + 2 * C::MB, t = y / C::MB, mb = y % C::MB;
+        return __builtin_bit_cast(bf16x8_t, *(const u32x4 *)(Vs + buf(x >= xD ? it : it - 1) * C::VTILE + vbase +
+                                                            (32 * mb) * C::TRSE + 16 * t));
+    };
+
     f32x16_t o[C::MB];
-#pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb) o[mb] = f32x16_t{};
-    f32x16_t s[2];
-    bf16x8_t pb[4];
-    float m_run = -__builtin_inff();  // running max of scale*log2(e)*s (may lag by <= 8)
-    float l_run = 0.f;                // this lane's share of the running sum
+    float m_run, l_run;   // reference of the exponentials (log2 units); this lane's share of the running sum
     const float c2 = a.scale_log2;
 
-    // The row sum adds the bf16-rounded probabilities -- exactly the P the
-    // value product consumes -- two at a time (v_dot2 against (1, 1)), in two
-    // chains: half the VALU instructions of fp32 adds.  Read in place
-    // (PAGED), it runs at the end of the MFMA phase that consumes P, where the
-    // wave's VALU is otherwise idle (pinned: the P registers are redefined
-    // after the barrier): 3% faster for that instantiation, while the one over
-    // a compact copy measured 2.5% slower that way and keeps it in the
-    // softmax.
-    auto row_sum = [&](bool pin_p) {
-        if (pin_p) {
+    bool every = false;   // take every tile's row maximum
+    for (;;) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                i16x4_t *w = (i16x4_t *)&pb[t];
-                __asm__ volatile("" : "+v"(w[0]), "+v"(w[1]));
-            }
-        }
-        float l2 = 0.f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bf16x2_t pr = {pb[t][2 * j], pb[t][2 * j + 1]};
-                if (t & 1) l2 = __builtin_amdgcn_fdot2_f32_bf16(pr, kOnes2, l2, false);
-                else l_run = __builtin_amdgcn_fdot2_f32_bf16(pr, kOnes2, l_run, false);
-            }
-        l_run += l2;
-    };
+        for (int mb = 0; mb < C::MB; ++mb) o[mb] = f32x16_t{};
+        m_run = -__builtin_inff();
+        l_run = 0.f;
+        f32x16_t s[2];
+        bf16x8_t pb[4];
+        bf16x8_t fr[kPrefetch];
 
-    auto softmax = [&](int j0) {
-        if (j0 + BN > Lk) {
-            // keys past Lk score -inf.  The in-place kernel does it with a sign
-            // mask per entry: compares would hold 32 lane masks (SGPR pairs) at
-            // once and push its SGPRs into spills (55 -> 2 spilled, its 480P
-            // launch 1.1% faster); for the other kernel the compares measured
-            // 1.3% faster.
-            if constexpr (PAGED) {
-                const int room = Lk - 1 - (j0 + 4 * hl);
+        // Prologue: the first two tiles into LDS, the third into registers.
+        auto cursor_at = [&](int j0) {
+            PageCursor cu{j0, 0, 0, 0u};
+            if (PAGED && j0 < kvl) {
+                cu.y = div_piece(a, j0);
+                cu.r = j0 - cu.y * P;
+                cu.off = piece_off(cu.y, cu.r);
+            }
+            return cu;
+        };
+        PageCursor cu = cursor_at(ragged ? (T - 1) * BN : kt0 * BN);
+        one_tile(cu);
+        // the others go on at kt0 + 1, or at kt0 where the last tile came first
+        if (ragged && kt0 < T - 1) cu = cursor_at(kt0 * BN);
+        else advance(cu);
+        // (past the segment's end the order goes on over valid tiles, never stored)
+        auto fetch = [&]() {
+            if (left == 0 && Tw > 0) next_run(cu);
+            load();
+        };
+        // (both tiles' loads in flight together)
+        load();
+        u32x4 k0[C::NV];
+        Words<C::VW> v0[4];
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+        for (int i = 0; i < C::NV; ++i) k0[i] = kst[i];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const uint32_t past = (uint32_t)((room - (kb * 32 + 8 * (i >> 2) + (i & 3))) >> 31);
-                        s[kb][i] = __uint_as_float((past & 0xff800000u) | (~past & __float_as_uint(s[kb][i])));
-                    }
+        for (int r = 0; r < 4; ++r) v0[r] = vst[r];
+        fetch();
+#pragma unroll
+        for (int x = 0; x < kStores; ++x) store(x, 0, k0, v0);
+#pragma unroll
+        for (int x = 0; x < kStores; ++x) store(x, 1, kst, vst);
+        fetch();
+        __syncthreads();
+        // Let every outstanding load (the Q fragments included) land once here, so
+        // the loop's score products carry no wait on the staging loads in flight.
+        __builtin_amdgcn_s_waitcnt(0);
+
+        auto product = [&](int x, const bf16x8_t &f) {
+            if (x < xB || (x >= xC && x < xD)) {
+                const int kb = x >= xC, kk = kb ? x - xC : x;
+                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[kk], kk == 0 ? f32x16_t{} : s[kb], 0, 0, 0);
             } else {
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int key = j0 + kb * 32 + 8 * (i >> 2) + 4 * hl + (i & 3);
-                        if (key >= Lk) s[kb][i] = -__builtin_inff();
-                    }
+                const int y = x >= xD ? x - xD : x - xB + 2 * C::MB, t = y / C::MB, mb = y % C::MB;
+                o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pb[t], o[mb], 0, 0, 0);
             }
-        }
-        float mx = fmaxf(s[0][0], s[0][1]);
-#pragma unroll
-        for (int i = 2; i < 16; ++i) mx = fmaxf(mx, s[0][i]);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[1][i]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32)) * c2;
-        if (__ballot(mx > m_run + kRescaleSlack)) {
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-            l_run *= alpha;
-#pragma unroll
-            for (int mb = 0; mb < C::MB; ++mb) o[mb] *= alpha;
-        }
+        };
         // P^T as the B operand: k-step t covers keys 16t + {4hl..4hl+3, 8+4hl..8+4hl+3},
-        // i.e. accumulator entries s[t/2][8*(t%2) + j].
+        // i.e. accumulator entries s[t/2][8*(t%2) + j]; pair p is entries 2p, 2p + 1 in that order.
+        float e0, e1, m_exp;
+        auto exp_pair = [&](int p) {
+            const int t = p >> 2, j = 8 * (t & 1) + 2 * (p & 3);
+            e0 = __builtin_amdgcn_exp2f(fmaf(s[t >> 1][j], c2, -m_exp));
+            e1 = __builtin_amdgcn_exp2f(fmaf(s[t >> 1][j + 1], c2, -m_exp));
+        };
+        auto round_pair = [&](int p) {
+            const int t = p >> 2, j = 2 * (p & 3);
+            pb[t][j] = (__bf16)e0;
+            pb[t][j + 1] = (__bf16)e1;
+        };
+        // The row sum adds the bf16-rounded probabilities -- exactly the P the
+        // value product consumes -- two at a time, in two chains.
+        float l2 = 0.f;
+        auto sum_pair = [&](int p) {
+            const int t = p >> 2, j = 2 * (p & 3);
+            const bf16x2_t pr = {pb[t][j], pb[t][j + 1]};
+            if (t & 1) l2 = __builtin_amdgcn_fdot2_f32_bf16(pr, kOnes2, l2, false);
+            else l_run = __builtin_amdgcn_fdot2_f32_bf16(pr, kOnes2, l_run, false);
+        };
+        int it = 0;
+        // Row maximum of the tile whose scores s holds, in log2 units.
+        auto row_max = [&](const f32x16_t &s0, const f32x16_t &s1) {
+            float mx = fmaxf(s0[0], s0[1]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+            for (int i = 2; i < 16; ++i) mx = fmaxf(mx, s0[i]);
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                pb[t][j] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[t >> 1][8 * (t & 1) + j], c2, -m_run));
-        if constexpr (!PAGED) row_sum(false);
-    };
-
-    // Prologue: group 0 copies K(0) and K(1) into LDS, group 1 copies V(0);
-    // then group 1 fetches K(2) and group 0 fetches V(1) into registers, and
-    // group 0 computes S(0).
-    u32x4 stage[4];
-    if (grp == 0) {
-        load_k(tile0(0), stage);
-        store_k(Ks[0], stage);
-        if (n > 1) {
-            load_k(tile0(1), stage);
-            store_k(Ks[1], stage);
+            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s1[i]);
+            return fmaxf(mx, __shfl_xor(mx, 32)) * c2;
+        };
+        // Pair of probabilities formed in step x: those of key block 0 from its
+        // second step after run A on, those of key block 1 from the second after run
+        // C; the last ones (from kLate on) in run A of the next iteration.
+        constexpr int kLate = D == 128 ? 12 : 11;
+        auto pair_at = [](int x) -> int {
+            if (D == 128) return x < 8 ? (x % 2 == 0 ? 12 + x / 2 : -1) : (x >= 9 && x % 2 == 1 ? (x - 9) / 2 : -1);
+            return x <= 4 ? 11 + x : x - 5;
+        };
+        // The tile stored in this iteration is visible to the others from here on.  LDS
+        // operations finish in order and kPrefetch operand reads follow the stores, so
+        // at most kPrefetch outstanding ones means that the stores are done; the reads
+        // themselves stay in flight.
+        auto tile_barrier = [&]() {
+            __asm__ volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(kPrefetch) : "memory");
+        };
+        // steps [x0, x1) alone
+        auto run = [&](int x0, int x1) {
+            bf16x8_t f[2];
+            f[0] = read_a(x0, it);
+#pragma unroll
+            for (int x = x0; x < x1; ++x) {
+                if (x + 1 < x1) f[(x + 1 - x0) & 1] = read_a(x + 1, it);
+                product(x, f[(x - x0) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // the value products of key block 1 of the tile before
+        // (m_exp opaque in every iteration: else the compiler takes the exponentials
+        // that both ways on from an iteration begin with into its end)
+        auto set_m = [&]() {
+            m_exp = m_run;
+            __asm__ volatile("" : "+v"(m_exp));
+        };
+        // P formed here, not where the next iteration first needs it
+        auto pin_p = [&](int t) { __asm__ volatile("" : "+v"(pb[t])); };
+        auto finish_tile = [&]() {
+            set_m();
+#pragma unroll
+            for (int p = kLate; p < 16; ++p) {
+                exp_pair(p);
+                round_pair(p);
+                sum_pair(p);
+            }
+            run(xB, xC);
+        };
+        // The first tile: its runs in turn, its row maximum (keys past Lk masked) the
+        // reference of the exponentials.
+#pragma unroll
+        for (int x = 0; x < kStores; ++x) store(x, buf(it + 2), kst, vst);
+        run(0, xB);
+        run(xC, xD);
+        if (ragged) {
+            const int room = Lk - 1 - ((T - 1) * BN + 4 * hl);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const uint32_t past = (uint32_t)((room - (kb * 32 + 8 * (i >> 2) + (i & 3))) >> 31);
+                    s[kb][i] = __uint_as_float((past & 0xff800000u) | (~past & __float_as_uint(s[kb][i])));
+                }
         }
-        if (n > 1) load_v(tile0(1), stage);
-    } else {
-        load_v(tile0(0), stage);
-        store_vt(Vs[0], stage);
-        if (n > 2) load_k(tile0(2), stage);
-    }
-    __syncthreads();
-    if (grp == 0) mfma_block<D, false, true>(nullptr, Ks[0], vbase, kbase, pb, qf, o, s);
-
-    // Both groups run the same loop body -- softmax of tile j, barrier, MFMA
-    // block (P(j)V(j), then S(j+1) = K(j+1)Q^T), barrier -- with group 1 one
-    // phase behind group 0, so on every SIMD one wave's softmax overlaps the
-    // other wave's MFMA block.  In global phase terms:
-    //   phase 2j:   group 0 softmax(j)     | group 1 MFMA block of tile j-1
-    //   phase 2j+1: group 0 MFMA block j   | group 1 softmax(j)
-    // K(j) is read in phases 2j-1 and 2j from Ks[j%2]; V(j) in phases 2j+1 and
-    // 2j+2 from Vs[j%2].  Group 0 stores V(j) during its softmax(j) and fetches
-    // V(j+1); group 1 stores K(j+2) during its softmax(j) and fetches K(j+3).
-    // Every store lands in a buffer whose previous tile was last read before the
-    // preceding barrier and is first read after the next one.  The MFMA block of
-    // the last tile also runs the score product on a stale K buffer; its result
-    // is never used.  Both groups meet 2*n + 1 barriers, the last one after
-    // every LDS read of the segment.
-    if (grp == 1) {
-        mfma_block<D, false, true>(nullptr, Ks[0], vbase, kbase, pb, qf, o, s);
-        __syncthreads();
-    }
-    // Let every outstanding load (the Q fragments included) land once here, so
-    // the loop's score products carry no wait on the staging loads in flight.
-    __builtin_amdgcn_s_waitcnt(0);
-    // paged: group 0's next V tile is position 2, group 1's next K tile
-    // position 3; both cursors are kept (uniform, scalar) and advanced together
-    PageCursor cur_v = PAGED && n > 2 ? cursor_at(2) : PageCursor{0, 0, 0, 0u};
-    PageCursor cur_k = PAGED && n > 3 ? cursor_at(3) : PageCursor{0, 0, 0, 0u};
-    for (int it = 0; it < n; ++it) {
-        const int j0 = tile0(it);
-        softmax(j0);
-        if (grp == 0) {
-            if (it >= 1) store_vt(Vs[it & 1], stage);
-            if (it >= 1 && it + 1 < n) {
-                if constexpr (PAGED) {
-                    if (gtid < C::VUNITS)
-                        load_tile_cursor<D, 4>(Vc, ktab, P, cur_v, Vq, kvl, Lk, Lq, stage, voffv, D * 2);
-                } else {
-                    load_v(tile0(it + 1), stage);
+        m_run = row_max(s[0], s[1]);
+        set_m();
+#pragma unroll
+        for (int p = 0; p < kLate; ++p) {
+            exp_pair(p);
+            round_pair(p);
+            sum_pair(p);
+        }
+        run(xD, NSTEP);
+#pragma unroll
+        for (int i = 0; i < kPrefetch; ++i) fr[i] = read_a(NSTEP + i, it);
+        fetch();
+        ++it;
+        tile_barrier();
+        // The others.  Per step one product, the read of a later step's operand and a
+        // share of the tile's other work, pinned in this order.
+        while (it < n) {
+            if (every) {
+                // The running max moves where this tile's exceeds it by more than
+                // kRescaleSlack, by whole powers of two; what the previous tile still has
+                // to do takes the new one.
+                run(0, xB);
+                float mx = row_max(s[0], s[0]);
+#pragma unroll
+                for (int kk = 0; kk < C::KS; ++kk)
+                    s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_a(xC + kk, it), qf[kk],
+                                                                   kk == 0 ? f32x16_t{} : s[0], 0, 0, 0);
+                mx = fmaxf(mx, row_max(s[0], s[0]));
+                if (__ballot(mx > m_run + kRescaleSlack)) {
+                    const float up = mx > m_run + kRescaleSlack ? ceilf(mx - m_run) : 0.f;
+                    const float alpha = __builtin_amdgcn_exp2f(-up);
+                    l_run *= alpha;
+                    l2 *= alpha;
+#pragma unroll
+                    for (int mb = 0; mb < C::MB; ++mb) o[mb] *= alpha;
+#pragma unroll
+                    for (int p = 8; p < kLate; ++p) {
+                        exp_pair(p);
+                        e0 *= alpha;
+                        e1 *= alpha;
+                        round_pair(p);
+                    }
+                    m_run += up;
                 }
             }
-        } else {
-            if (it + 2 < n) store_k(Ks[it & 1], stage);
-            if (it + 3 < n) {
-                if constexpr (PAGED) {
-                    load_tile_cursor<D, C::NV>(Kc, ktab, P, cur_k, Kq, kvl, Lk, Lq, stage, voff, C::RPP * D * 2);
-                } else {
-                    load_k(tile0(it + 3), stage);
+            set_m();
+#pragma unroll
+            for (int x = 0; x < NSTEP; ++x) {
+                product(x, fr[x % kPrefetch]);
+                fr[x % kPrefetch] = read_a(x + kPrefetch, it);
+                const int p0 = x > 0 ? pair_at(x - 1) : -1, p = pair_at(x);
+                if (p0 >= 0) {
+                    round_pair(p0);
+                    sum_pair(p0);
                 }
+                if (p >= 0) exp_pair(p);
+                if (x == NSTEP - 1 && p >= 0) {
+                    round_pair(p);
+                    sum_pair(p);
+                }
+                constexpr int kS = D == 128 ? 2 : 1;
+                if (x >= xC && (x - xC) % kS == 0 && (x - xC) / kS < kStores) store((x - xC) / kS, buf(it + 2), kst, vst);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            pin_p(2);
+            fetch();
+            ++it;
+            tile_barrier();
         }
-        if constexpr (PAGED) {
-            if (it >= 1) advance(cur_v);
-            advance(cur_k);
-        }
+        // (`it` has moved on: the last tile is "the tile before")
+        finish_tile();
+        l_run += l2;
+
+        if (every) break;
+        // redo?
+        float z = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) z = fmaf(o[mb][i], 0.f, z);
+        if (__ballot(qok && !(l_run <= kSumLimit && z == 0.f)) && lane == 0) *redo = 1;
         __syncthreads();
-        // (no wave-priority raise around the block: measured 1% slower with it)
-        mfma_block<D, true, true>(Vs[it & 1], Ks[(it + 1) & 1], vbase, kbase, pb, qf, o, s);
-        if constexpr (PAGED) row_sum(true);
+        if (__builtin_amdgcn_readfirstlane((int)*(volatile uint32_t *)redo) == 0) break;
         __syncthreads();
+        if (tid == 0) *redo = 0;
+        every = true;
     }
-    if (grp == 0) __syncthreads();
 
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     const float inv = 1.f / l_tot;
@@ -639,8 +761,11 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t (&Ks)[2
                 put_shared(op + ((wave * C::MB + mb) * 4 + g) * 64 + lane, v);
             }
         if (hl == 0) {
-            put_shared(slot + BM * D / 2 + wave * 32 + l32, m_run);
-            put_shared(slot + BM * D / 2 + BM + wave * 32 + l32, l_tot);
+            // a sum far above one hands its exponent to the maximum: the weights by
+            // which the merge multiplies outputs stay small
+            const int e = l_tot > 0x1p24f ? __builtin_amdgcn_frexp_expf(l_tot) : 0;
+            put_shared(slot + BM * D / 2 + wave * 32 + l32, m_run + (float)e);
+            put_shared(slot + BM * D / 2 + BM + wave * 32 + l32, __builtin_amdgcn_ldexpf(l_tot, -e));
         }
         return;
     }
@@ -666,50 +791,72 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t (&Ks)[2
 template <int D, bool BAL, bool PAGED>
 __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnArgs a) {
     using C = Cfg<D>;
-    __shared__ __attribute__((aligned(16))) uint16_t Ks[2][C::TILE];
-    __shared__ __attribute__((aligned(16))) uint16_t Vs[2][C::VTILE];
-    __shared__ uint32_t flag;
+    __shared__ __attribute__((aligned(16))) uint16_t Ks[kBufs * C::TILE];
+    __shared__ __attribute__((aligned(16))) uint16_t Vs[kBufs * C::VTILE];
+    __shared__ uint32_t flag, redo;
+    if (threadIdx.x == 0) redo = 0;   // (barriers follow before its first use)
 
     if (!BAL) {
         const int item = (blockIdx.x & 7) * a.items_per_xcd + (blockIdx.x >> 3);
         if (item >= a.n_items) return;
         const int li = item / a.n_qtiles;
-        attn_segment<D, PAGED>(a, Ks, Vs, li, item - li * a.n_qtiles, 0, entry_tiles<PAGED>(a, li), 0, nullptr);
+        attn_segment<D, PAGED>(a, Ks, Vs, &redo, li, item - li * a.n_qtiles, 0, entry_tiles<PAGED>(a, li), 0, nullptr);
         return;
     }
     const WorkList wl = work_list<PAGED>(a);
     const Schedule sc = make_schedule(a, wl);
     const int r = (blockIdx.x & 7) * (a.n_blocks >> 3) + (blockIdx.x >> 3);
-    if (r >= sc.G) return;
-    const int64_t end = sc.start(r + 1);
-    int64_t cur = sc.start(r);
+    if (sc.total == 0) return;
+    // this workgroup's segments: one part of an item, or a range over items
+    const int parts = whole_parts(a, wl, sc);
+    if (!parts && r >= sc.G) return;
+    int64_t cur = parts ? 0 : sc.start(r);
+    const int64_t end = parts ? 1 : sc.start(r + 1);
     bool first = true;
     while (cur < end) {
-        // locate the item holding tile `cur`
-        const ItemPos ip = locate(wl, cur);
-        const int qt = ip.qt, T = ip.T;
-        const int64_t ibase = ip.ibase;
-        const int t0 = (int)(cur - ibase);
-        const int t1 = (int)((end < ibase + T ? end : ibase + T) - ibase);
-        float *slot = (t0 == 0 && t1 == T)
-                          ? nullptr
-                          : a.part + (size_t)(2 * r + (first ? 0 : 1)) * slot_floats<D>();
-        // Rotate the item's key tiles so that its first part, started at time
-        // tau0 = ibase - start(owner(ibase)) of its workgroup, reads key tile
-        // tau mod T at time tau: the first parts of all items of a head then
-        // sweep its K/V in step (later parts in step among themselves, shifted
-        // by a range length), so the XCD's L2 serves the re-reads.
-        const int rot = (int)((ibase - sc.start(sc.owner(ibase))) % T);
-        attn_segment<D, PAGED>(a, Ks, Vs, ip.li, qt, t0, t1, rot, slot);
+        int li, qt, t0, t1, rot, b0, n_parts, s0;
+        if (parts) {
+            const int item = r / parts, j = r - item * parts;
+            if (item >= a.n_items) return;
+            li = item / a.n_qtiles;
+            qt = item - li * a.n_qtiles;
+            const int T = __builtin_amdgcn_readlane(wl.T, li);
+            n_parts = min(parts, T);
+            if (j >= n_parts) return;
+            t0 = (int)((int64_t)T * j / n_parts);
+            t1 = (int)((int64_t)T * (j + 1) / n_parts);
+            rot = 0;
+            b0 = item * parts;
+            s0 = 2 * b0;
+            cur = end;
+        } else {
+            // locate the item holding tile `cur`
+            const ItemPos ip = locate(wl, cur);
+            const int64_t ibase = ip.ibase;
+            li = ip.li;
+            qt = ip.qt;
+            t0 = (int)(cur - ibase);
+            t1 = (int)((end < ibase + ip.T ? end : ibase + ip.T) - ibase);
+            b0 = sc.owner(ibase);
+            n_parts = sc.owner(ibase + ip.T - 1) - b0 + 1;
+            s0 = first_slot(sc, ibase);
+            // Rotate the item's key tiles so that its first part, started at time
+            // tau0 = ibase - start(b0) of its workgroup, reads key tile tau mod T at
+            // time tau: the first parts of all items of a head then sweep its K/V in
+            // step (later parts in step among themselves, shifted by a range length),
+            // so the XCD's L2 serves the re-reads.
+            rot = (int)((ibase - sc.start(b0)) % ip.T);
+            cur = ibase + t1;
+        }
+        float *slot = n_parts == 1 ? nullptr : a.part + (size_t)(2 * r + (first ? 0 : 1)) * slot_floats<D>();
+        attn_segment<D, PAGED>(a, Ks, Vs, &redo, li, qt, t0, t1, rot, slot);
         if (slot) {
             // the last of the item's parts to arrive combines them (no wait:
             // every other part is complete when its workgroup arrives)
-            const int n_parts = sc.owner(ibase + T - 1) - sc.owner(ibase) + 1;
-            uint32_t *cnt = a.item_counters + (size_t)(ip.li * a.n_qtiles + qt) * kItemCounterStride;
+            uint32_t *cnt = a.item_counters + (size_t)(li * a.n_qtiles + qt) * kItemCounterStride;
             if (arrive_last(cnt, (uint32_t)n_parts, &flag))
-                merge_rows<D, 64>(a, sc, ip.li, qt, ibase, T, threadIdx.x >> 6, threadIdx.x & 63);
+                merge_rows<D, 64>(a, b0, b0 + n_parts - 1, s0, li, qt, threadIdx.x >> 6, threadIdx.x & 63);
         }
-        cur = ibase + t1;
         first = false;
     }
 }
@@ -833,9 +980,8 @@ __global__ __launch_bounds__(kThreads, 4) void attn_mass_kernel(AttnArgs a) {
                 store(Ks[(it + 1) & 1]);    // last read before the barrier just passed
                 if (p2.b < b1) load(p2);
             }
-            f32x16_t o[C::MB], s[2];
-            bf16x8_t pb[4];
-            mfma_block<D, false, true>(nullptr, Ks[it & 1], 0, kbase, pb, qf, o, s);
+            f32x16_t s[2];
+            score_block<D>(Ks[it & 1], kbase, qf, s);
             // keys of this lane: j + 32kb + 8(i/4) + 4hl + i%4
             if (p.j + BN > p.hi) {
 #pragma unroll

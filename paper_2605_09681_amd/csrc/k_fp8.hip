@@ -804,7 +804,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fp8_kernel(AttnArgs a) {
             const int n_parts = sc.owner(ibase + T - 1) - sc.owner(ibase) + 1;
             uint32_t *cnt = a.item_counters + (size_t)(ip.li * a.n_qtiles + qt) * kItemCounterStride;
             if (arrive_last(cnt, (uint32_t)n_parts, &flag))
-                merge_rows<D, 64>(a, sc, ip.li, qt, ibase, T, threadIdx.x >> 6, threadIdx.x & 63);
+                merge_rows<D, 64>(a, sc.owner(ibase), sc.owner(ibase + T - 1), first_slot(sc, ibase), ip.li, qt,
+                                  threadIdx.x >> 6, threadIdx.x & 63);
         }
         cur = ibase + t1;
         first = false;
