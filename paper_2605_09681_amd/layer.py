@@ -21,7 +21,8 @@ of one layer.  The four stages of the method:
   (default priority) next to the dynamic heads' scoring and attention;
 * ``"compact"``: the static heads attended in place (or gathered first) on a
   side stream while the dynamic heads are scored, compacted into Kc/Vc and
-  attended on the current stream.
+  attended on the current stream; where that hides less than it costs
+  (OVERLAP_BYTES), every head gathered and attended on the current stream.
 
 The individual stages enqueue on the current torch stream; nothing
 synchronises with the host.
@@ -56,6 +57,24 @@ def paged_supported(dtype, frame_tokens: int, seg_tokens: int, cap_frames: int) 
     piece = min(seg_tokens, frame_tokens)
     return (static_in_place_supported(dtype, frame_tokens) and piece >= 64
             and cap_frames * (frame_tokens // piece) <= 256)
+
+
+# Key bytes of the dynamic heads' history from which a compacting bf16 step runs
+# the static heads on a second stream, next to the scoring and the compaction.
+# The two stream waits cost about 60 us of host time and keep the GPU from
+# running the launches back to back; they hide the scoring and the compaction.
+# Two streams against one: 83 KB 139 and 57 us, 2.4 MB 244 and 240, 5 MB 128 and
+# 61, 15 MB 127 and 84; 53 MB 556 and 592, 88 MB 278 and 315, 140 MB 3225 and
+# 3283.  fp32 steps, whose attention is far longer than all the rest, measured
+# the same or slower with two (26 MB 381-405 and 394, 106 MB 4900 and 4705), and
+# so did compress(), which has no attention to hide behind (53 MB 124 and 90,
+# 276 MB 472 and 470): these always take one.
+OVERLAP_BYTES = 20 << 20
+
+
+def _overlap_pays(types, H: int, F: int, d: int, dtype) -> bool:
+    n_dyn = sum(t == FKV_DYNAMIC for t in types)
+    return dtype == torch.bfloat16 and n_dyn * (H + 1) * F * d * 2 >= OVERLAP_BYTES
 
 
 class CompressedLayer:
@@ -97,6 +116,10 @@ class CompressedLayer:
         # side stream for the static heads (only when both head types exist)
         self.side = (torch.cuda.Stream(device=dev) if overlap and self.has_static and self.has_dynamic
                      else None)
+        # (a caller's slab may hold the dynamic heads alone: then there is no room to gather static ones)
+        self.two_streams = self.side is not None and (
+            self.slab < slab_tokens(self.shape, self.heads)
+            or _overlap_pays(self.types, hist_frames, frame_tokens, head_dim, self.dtype))
         self.static_heads = [h for h, t in enumerate(self.types) if t == FKV_STATIC]
         self.dynamic_heads = [h for h, t in enumerate(self.types) if t == FKV_DYNAMIC]
         if self.side is not None and self.attn_workspace is not None:
@@ -179,17 +202,6 @@ class CompressedLayer:
 
     # whole step --------------------------------------------------------------
     def compress(self, K_hist, V_hist, frame_slot, K_cur):
-        if self.side is not None:
-            main = torch.cuda.current_stream(self.device)
-            self.side.wait_stream(main)             # inputs written on the main stream
-            with torch.cuda.stream(self.side):
-                self.compress_static(K_hist, V_hist, frame_slot)
-            for t in (K_hist, V_hist):              # read on the side stream too
-                t.record_stream(self.side)
-            self.score(K_hist, frame_slot, K_cur)
-            self.select_compact(K_hist, V_hist, frame_slot)
-            main.wait_stream(self.side)             # attention reads every head's Kc/Vc/kv_len
-            return
         if self.has_dynamic:
             self.score(K_hist, frame_slot, K_cur)
             self.select_compact(K_hist, V_hist, frame_slot)
@@ -247,7 +259,8 @@ class CompressedLayer:
             mark("dynamic_attention", 1, main)
             main.wait_stream(self.side)
             return
-        if self.side is None:
+        two = self.two_streams
+        if self.side is None or not (two or events):
             cur = torch.cuda.current_stream(self.device)
             if self.static_in_place and not self.has_dynamic:
                 mark("attention", 0, cur)
@@ -261,27 +274,31 @@ class CompressedLayer:
             return
         main = torch.cuda.current_stream(self.device)
         args = (self.Kc, self.Vc, self.kv_len, K_cur, V_cur, self.scale, O, lse)
-        self.side.wait_stream(main)
-        with torch.cuda.stream(self.side):
+        side = self.side if two else main
+        if two:
+            side.wait_stream(main)
+        with torch.cuda.stream(side):
             if self.static_in_place:
-                mark("static_attention", 0, self.side)
+                mark("static_attention", 0, side)
                 self.attention_static(K_hist, V_hist, frame_slot, Q, K_cur, V_cur, O, lse, self.attn_workspace2)
-                mark("static_attention", 1, self.side)
+                mark("static_attention", 1, side)
             else:
                 self.compress_static(K_hist, V_hist, frame_slot)
-                mark("static_attention", 0, self.side)
+                mark("static_attention", 0, side)
                 fkv_chunk_attention_heads(self.shape, self.static_heads, Q, *args[:7], lse=lse,
                                           workspace=self.attn_workspace2)
-                mark("static_attention", 1, self.side)
-        for t in (K_hist, V_hist, Q, K_cur, V_cur, O) + ((lse,) if lse is not None else ()):
-            t.record_stream(self.side)
+                mark("static_attention", 1, side)
+        if two:
+            for t in (K_hist, V_hist, Q, K_cur, V_cur, O) + ((lse,) if lse is not None else ()):
+                t.record_stream(side)
         self.score(K_hist, frame_slot, K_cur)
         self.select_compact(K_hist, V_hist, frame_slot)
         mark("dynamic_attention", 0, main)
         fkv_chunk_attention_heads(self.shape, self.dynamic_heads, Q, *args[:7], lse=lse,
                                   workspace=self.attn_workspace)
         mark("dynamic_attention", 1, main)
-        main.wait_stream(self.side)
+        if two:
+            main.wait_stream(side)
 
 
 class HeadProfiler:
@@ -477,6 +494,8 @@ class RolloutStack:
             return
         main = torch.cuda.current_stream(self.device)
         side = self.side if (self.side is not None and has_static and has_dynamic) else None
+        if not _overlap_pays(types, H, self.F, self.d, Kh.dtype):
+            side = None
         att = (self.Kc, self.Vc, self.kv_len, K_cur, V_cur, self.scale, O)
         if side is not None:
             static_ids = [h for h, t in enumerate(types) if t == FKV_STATIC]
