@@ -23,8 +23,8 @@
 // is looked up in its head's kept frames or kept segments, in the order the
 // compressed copy would hold them, so both give the same bytes.
 //
-// Attention: the bf16 kernel's structure (two ping-ponging 4-wave groups, 32
-// query rows per wave, 64-key tiles, balanced schedule, cut items combined by
+// Attention: the bf16 kernel's structure (8 waves of 32 query rows, 64-key tiles,
+// one pinned instruction stream per tile, balanced schedule, cut items combined by
 // the workgroup whose part arrives last) with
 //   S^T = K Q^T    2 x (d/64) MFMAs 32x32x64 per tile (A = K tile from LDS,
 //                  lane l reads 32 bytes of key row l%32 at dims 64ks + 32(l/32));
@@ -44,6 +44,16 @@
 // half h of A with byte j of lane half h of B), so any consistent assignment of
 // the contraction index to bytes is valid; this was checked on the hardware.
 // Output: O = O^T * s_v[d] / l (bf16), lse = ln2 * (m - 6) + ln l.
+//
+// An iteration issues the value products of the tile before and the score products
+// of the next one (9 products, 576 cycles of a wave's 64-key tile) with this tile's
+// 32 exponentials, their scaling and conversions (110 VALU instructions) behind
+// them.  E4M3 leaves the probabilities no room above the row maximum, so every
+// tile's is taken, the half of key block 0 in the iteration before; where it moves
+// the reference, outputs and normaliser follow one iteration later.
+// Bound: both pipes, at the clock that their power holds (480P launch: products in
+// 42% of the cycles at 1.99 GHz, 38% at 2.10 with the products of one wave group
+// beside the softmax of the other).  480P FP8 step 448 -> 428 us.
 #include "attn_common.h"
 #include "attn_merge.h"
 
@@ -56,7 +66,6 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 512;
-constexpr int kGroupThreads = 256;
 constexpr float kSlack = 2.f;   // log2 units the running max may lag behind
 constexpr float kPBias = 6.f;   // P' = 2^(x - m + kPBias) <= 2^(kSlack + kPBias)
 constexpr float kE4M3Max = 448.f;
@@ -463,8 +472,7 @@ struct Fp8Cfg {
     static constexpr int VTILE = D * VROW;
     static constexpr int KCH = D / 16;              // 16-byte chunks per K row
     static constexpr int VCH = BN / 16;             // 16-byte chunks per V^T row
-    static constexpr int NV = BN * D / 16 / kGroupThreads;  // staging vectors per thread
-    static_assert(NV >= 1 && NV <= 4, "tile shape");
+    static_assert(BN * D / 16 <= kThreads, "one staged vector per thread");
 };
 
 __device__ __forceinline__ i32x8 load32(const uint8_t *p) {
@@ -482,65 +490,13 @@ __device__ __forceinline__ f32x16_t mfma4x8(const i32x8 &a, const i32x8 &b, cons
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 4, 0, 0, 0, 0, 0);
 }
 
-// One MFMA block of a wave: S^T = K Q^T for the next tile (its K operands kq
-// were read from LDS during the previous phase), then, if PV, O^T += V^T P'^T
-// and l += 1 P'^T for the current tile.  The V^T operands are read at the start
-// of the block and arrive while the score products run.
-template <int D, bool PV>
-__device__ __forceinline__ void mfma_block8(const uint8_t *vs, int vbase, const i32x8 &pb, const i32x8 &ones,
-                                            const i32x8 (&qf)[D / 64], const i32x8 (&kq)[D / 32],
-                                            f32x16_t (&o)[D / 32], f32x16_t &lacc, f32x16_t (&s)[2]) {
-    using C = Fp8Cfg<D>;
-    constexpr int NQ = 2 * C::KS;
-    constexpr int NEARLY = NQ < C::MB ? NQ : C::MB;   // V operands read before the score products
-    i32x8 va[C::MB];
-    if (PV) {
-#pragma unroll
-        for (int mb = 0; mb < NEARLY / 2; ++mb) va[mb] = load32(vs + vbase + mb * 32 * C::VROW);
-    }
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) {
-        const int kk = i >> 1, kb = i & 1;
-        s[kb] = mfma8(kq[i], qf[kk], kk == 0 ? f32x16_t{} : s[kb]);
-        // the rest of the V operands, issued as the K operands retire
-        const int mb = NEARLY / 2 + i;
-        if (PV && mb < C::MB) va[mb] = load32(vs + vbase + mb * 32 * C::VROW);
-    }
-    if (PV) {
-#pragma unroll
-        for (int mb = 0; mb < C::MB; ++mb) o[mb] = mfma8(va[mb], pb, o[mb]);
-        lacc = mfma4x8(ones, pb, lacc);
-    }
-    if (PV) {
-#pragma unroll
-        for (int mb = 0; mb < NEARLY / 2; ++mb) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (NEARLY / 2 + i < C::MB) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, C::MB + 1, 0);
-    } else {
-        __builtin_amdgcn_sched_group_barrier(0x008, NQ, 0);
-    }
-}
-
-// K operands of the score product for one tile: key rows 32kb + l32, dims
-// 64kk + 32hl .. +32 (index 2kk + kb).
-template <int D>
-__device__ __forceinline__ void read_kq(const uint8_t *ks, int kbase, i32x8 (&kq)[D / 32]) {
-    using C = Fp8Cfg<D>;
-#pragma unroll
-    for (int i = 0; i < 2 * C::KS; ++i) kq[i] = load32(ks + kbase + (i & 1) * 32 * C::KROW + 64 * (i >> 1));
-}
+constexpr int kBufs = 4;   // K and V^T tiles in LDS
 
 template <int D>
-__device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t (&Ks)[2][Fp8Cfg<D>::KTILE],
-                                            uint8_t (&Vs)[2][Fp8Cfg<D>::VTILE], int h, int qt, int t0, int t1,
+__device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint8_t *Vs, int h, int qt, int t0, int t1,
                                             int rot, float *slot) {
     using C = Fp8Cfg<D>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int grp = wave >> 2;
     const int l32 = lane & 31, hl = lane >> 5;
     const int Lq = a.Lq;
     const int n = t1 - t0;
@@ -557,43 +513,39 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t (&Ks)[2][
     for (int kk = 0; kk < C::KS; ++kk)
         qf[kk] = qok ? load32(Qh + (size_t)qrow * D + 64 * kk + 32 * hl) : i32x8{};
 
+    // The segment's key tiles: kt0, kt0 + 1, ... (mod T); where the keys end inside
+    // tile T - 1 and it is one of them, it comes first, before the loop, with the
+    // keys past Lk masked; the others are full ones.
     const int Lk = head_kvl(a, h) + Lq;
     const int T = (Lk + BN - 1) / BN;
+    const int kt0 = (t0 + rot) % T;
+    const bool ragged = Lk % BN != 0 && T - 1 - kt0 < n;
+    const int Tw = max(Lk / BN, 1);   // the tiles that the order wraps over
     const uint8_t *K8 = (const uint8_t *)a.Kc + (size_t)h * a.fp8_rows * D;
     const uint8_t *V8 = (const uint8_t *)a.Vc + (size_t)h * a.fp8_rows * D;
 
-    const int gtid = tid & 255;
-    const int kt0 = (t0 + rot) % T;
-    auto tile = [&](int j) {
-        const int k = kt0 + j;
-        return k >= T ? k - T : k;
+    // A tile's K and V^T are BN * D contiguous bytes each: one 16-byte vector per
+    // thread (D = 64: half of the threads).  Two tiles are in flight, so a load has
+    // two iterations to arrive.
+    struct Stage {
+        u32x4 k, v;
     };
-    auto load_k = [&](int kt, u32x4 (&dst)[4]) {
-#pragma unroll
-        for (int i = 0; i < C::NV; ++i) {
-            const int v = gtid + i * kGroupThreads;
-            dst[i] = __builtin_nontemporal_load((const u32x4 *)(K8 + ((size_t)kt * BN + v / C::KCH) * D + 16 * (v % C::KCH)));
+    const bool stages = BN * D / 16 >= kThreads || tid < BN * D / 16;
+    int kt;   // next tile to fetch (past the segment's end: valid tiles, never used)
+    auto fetch = [&](Stage &st) {
+        if (stages) {
+            st.k = *(const u32x4 *)(K8 + (size_t)kt * (BN * D) + 16 * tid);
+            st.v = *(const u32x4 *)(V8 + (size_t)kt * (BN * D) + 16 * tid);
         }
+        kt = kt + 1 >= Tw ? 0 : kt + 1;
     };
-    auto load_v = [&](int kt, u32x4 (&dst)[4]) {
-#pragma unroll
-        for (int i = 0; i < C::NV; ++i) {
-            const int v = gtid + i * kGroupThreads;
-            dst[i] = __builtin_nontemporal_load((const u32x4 *)(V8 + (size_t)kt * BN * D + 16 * v));
-        }
-    };
-    auto store_k = [&](uint8_t *t, const u32x4 (&src)[4]) {
-#pragma unroll
-        for (int i = 0; i < C::NV; ++i) {
-            const int v = gtid + i * kGroupThreads;
-            *(u32x4 *)(t + (v / C::KCH) * C::KROW + 16 * (v % C::KCH)) = src[i];
-        }
-    };
-    auto store_v = [&](uint8_t *t, const u32x4 (&src)[4]) {
-#pragma unroll
-        for (int i = 0; i < C::NV; ++i) {
-            const int v = gtid + i * kGroupThreads;
-            *(u32x4 *)(t + (v / C::VCH) * C::VROW + 16 * (v % C::VCH)) = src[i];
+    const int kofs = (tid / C::KCH) * C::KROW + 16 * (tid % C::KCH);
+    const int vofs = (tid / C::VCH) * C::VROW + 16 * (tid % C::VCH);
+    auto buf = [](int tile) { return tile & (kBufs - 1); };
+    auto store = [&](int b, const Stage &st) {
+        if (stages) {
+            *(u32x4 *)(Ks + b * C::KTILE + kofs) = st.k;
+            *(u32x4 *)(Vs + b * C::VTILE + vofs) = st.v;
         }
     };
 
@@ -607,107 +559,170 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t (&Ks)[2][
     for (int mb = 0; mb < C::MB; ++mb) o[mb] = f32x16_t{};
     f32x16_t lacc = f32x16_t{};
     f32x16_t s[2];
-    i32x8 pb = i32x8{};
+    i32x8 pa = i32x8{}, pb = i32x8{};
     const i32x8 ones = {0x22222222, 0x22222222, 0x22222222, 0x22222222, 0, 0, 0, 0};  // E2M1 1.0
-    float m_run = -__builtin_inff();
 
-    // Row maximum of the current scores (keys past Lk masked), and the lazy
-    // update of the running max with the rescale of the accumulators.
-    auto row_max = [&](int j0) {
-        if (j0 + BN > Lk) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int key = j0 + kb * 32 + 8 * (i >> 2) + 4 * hl + (i & 3);
-                    if (key >= Lk) s[kb][i] = -__builtin_inff();
-                }
+    // Iteration it: the products of the tile before's values (V) and the next
+    // tile's scores (K), with this tile's probabilities formed behind them.  Steps:
+    // MB value products, KS score products of key block 0, the normaliser's, KS of
+    // key block 1.  Operand y of the iteration (the normaliser has none), y >= NOP:
+    // the next iteration's.
+    constexpr int NOP = C::MB + 2 * C::KS, NSTEP = NOP + 1;
+    constexpr int xK0 = C::MB, xL = xK0 + C::KS, xK1 = xL + 1;
+    constexpr int kRing = 4, kAhead = D == 128 ? 3 : 2;   // (no further than the next iteration's values)
+    constexpr int xStore = D == 128 ? 4 : 1;              // step of the LDS stores: two more operands are read after it
+    static_assert(NOP % kRing == 0 && kAhead <= C::MB, "operand ring");
+    auto read_a = [&](int y, int it) -> i32x8 {
+        if (y >= NOP || y < C::MB) {
+            const int mb = y >= NOP ? y - NOP : y;
+            return load32(Vs + buf(y >= NOP ? it : it - 1) * C::VTILE + vbase + mb * 32 * C::VROW);
         }
-        float mx = fmaxf(s[0][0], s[0][1]);
+        const int kb = (y - C::MB) / C::KS, kk = (y - C::MB) % C::KS;
+        return load32(Ks + buf(it + 1) * C::KTILE + kbase + kb * 32 * C::KROW + 64 * kk);
+    };
+    auto max16 = [&](const f32x16_t &v) {
+        float m = fmaxf(v[0], v[1]);
 #pragma unroll
-        for (int i = 2; i < 16; ++i) mx = fmaxf(mx, s[0][i]);
+        for (int i = 2; i < 16; ++i) m = fmaxf(m, v[i]);
+        return m;
+    };
+    // lanes l and l ^ 32 share a query
+    auto both = [&](float m) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+        return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    };
+    float m_run, bias;
+    // Half word w / 2 of P' (bytes 4(w/2) .. +3 of the B operand: accumulator entries
+    // s[w/8][..]): two probabilities.
+    auto exp_pair = [&](int w, i32x8 &p) {
+        const int kb = w >> 3, i0 = 2 * (w & 7);
+        const float e0 = __builtin_amdgcn_exp2f(fmaf(s[kb][i0], c2, bias));
+        const float e1 = __builtin_amdgcn_exp2f(fmaf(s[kb][i0 + 1], c2, bias));
+        const int old = p[w >> 1];   // both halves are overwritten: no zeroing move
+        p[w >> 1] = (w & 1) ? pk_fp8<true>(e0, e1, old) : pk_fp8<false>(e0, e1, old);
+    };
+    // Stores of this iteration are visible to the others from here on: LDS operations
+    // finish in order and at least two operands' reads (two each) follow the stores.
+    auto tile_barrier = [&]() {
+        __asm__ volatile("s_waitcnt lgkmcnt(4)\n\ts_barrier" ::: "memory");
+    };
+
+    // Prologue: tiles 0, 1 and 2 into LDS and registers, then the first tile's
+    // probabilities and the second one's scores.
+    Stage sa = {}, sb = {}, sc3 = {};
+    kt = ragged ? T - 1 : kt0;
+    fetch(sa);
+    if (ragged && kt0 < T - 1) kt = kt0;
+    fetch(sb);
+    fetch(sc3);
+    store(0, sa);
+    store(1, sb);
+    store(2, sc3);
+    fetch(sb);   // tile 3
+    fetch(sa);   // tile 4
+    __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[1][i]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32)) * c2;
-        if (__ballot(mx > m_run + kSlack)) {
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int kk = 0; kk < C::KS; ++kk)
+            s[kb] = mfma8(load32(Ks + kbase + kb * 32 * C::KROW + 64 * kk), qf[kk], kk == 0 ? f32x16_t{} : s[kb]);
+    if (ragged) {
+        const int room = Lk - 1 - ((T - 1) * BN + 4 * hl);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t past = (uint32_t)((room - (kb * 32 + 8 * (i >> 2) + (i & 3))) >> 31);
+                s[kb][i] = __uint_as_float((past & 0xff800000u) | (~past & __float_as_uint(s[kb][i])));
+            }
+    }
+    m_run = both(fmaxf(max16(s[0]), max16(s[1]))) * c2;
+    bias = kPBias - m_run;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) exp_pair(w, pa);
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int kk = 0; kk < C::KS; ++kk)
+            s[kb] = mfma8(load32(Ks + C::KTILE + kbase + kb * 32 * C::KROW + 64 * kk), qf[kk],
+                          kk == 0 ? f32x16_t{} : s[kb]);
+    float mx0 = max16(s[0]);
+    float alpha = 1.f;   // the last move of the reference, not yet applied to o and lacc
+    i32x8 fr[kRing];
+#pragma unroll
+    for (int y = 0; y < kAhead; ++y) fr[y] = read_a(y, 1);
+    // Let every outstanding load land once here, so the loop's products carry no
+    // wait on the staging loads in flight.
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    // One iteration; p: the tile before's probabilities, q: this tile's.
+    auto iteration = [&](int it, i32x8 &p, i32x8 &q, Stage &st) {
+        // the running max moves where the tile's exceeds it by more than kSlack;
+        // what it scales follows one iteration later, when the value products up to
+        // the tile before are in
+        if (__ballot(alpha != 1.f)) {
             lacc *= alpha;
 #pragma unroll
             for (int mb = 0; mb < C::MB; ++mb) o[mb] *= alpha;
         }
-    };
-    // The rounded probabilities P' of the current scores.
-    auto exps = [&]() {
-        const float bias = kPBias - m_run;
+        float mx = 0.f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            // bytes 4w .. 4w+3 of the B operand: accumulator entries s[w/4][4(w%4) .. +3]
-            const int kb = w >> 2, i0 = 4 * (w & 3);
-            int r = pb[w];  // both halves are overwritten: no zeroing move
-            r = pk_fp8<false>(__builtin_amdgcn_exp2f(fmaf(s[kb][i0], c2, bias)),
-                       __builtin_amdgcn_exp2f(fmaf(s[kb][i0 + 1], c2, bias)), r);
-            r = pk_fp8<true>(__builtin_amdgcn_exp2f(fmaf(s[kb][i0 + 2], c2, bias)),
-                       __builtin_amdgcn_exp2f(fmaf(s[kb][i0 + 3], c2, bias)), r);
-            pb[w] = r;
+        for (int x = 0; x < NSTEP; ++x) {
+            const int y = x < xL ? x : x - 1;   // operand of step x (xL has none)
+            if (x == xL) {
+                lacc = mfma4x8(ones, p, lacc);
+            } else {
+                if (x < xK0) o[x] = mfma8(fr[y % kRing], p, o[x]);
+                else if (x < xL) s[0] = mfma8(fr[y % kRing], qf[x - xK0], x == xK0 ? f32x16_t{} : s[0]);
+                else s[1] = mfma8(fr[y % kRing], qf[x - xK1], x == xK1 ? f32x16_t{} : s[1]);
+                fr[(y + kAhead) % kRing] = read_a(y + kAhead, it);
+            }
+            if (x == 0) {
+                mx = both(fmaxf(mx0, max16(s[1]))) * c2;
+                const float m_new = mx > m_run + kSlack ? mx : m_run;
+                alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                m_run = m_new;
+                bias = kPBias - m_run;
+            }
+            // key block 0 (pairs 0 .. 7) before its accumulators are written again in
+            // step xK0, key block 1 before step xK1
+            constexpr int n0 = xK0 - 1, n1 = xK1 - xK0;   // steps for each
+            if (x >= 1 && x < xK0)
+#pragma unroll
+                for (int w = (x - 1) * 8 / n0; w < x * 8 / n0; ++w) exp_pair(w, q);
+            if (x >= xK0 && x < xK1)
+#pragma unroll
+                for (int w = 8 + (x - xK0) * 8 / n1; w < 8 + (x - xK0 + 1) * 8 / n1; ++w) exp_pair(w, q);
+            if (x == xStore) {
+                store(buf(it + 2), st);
+                fetch(st);   // tile it + 4
+            }
+            if (x == NSTEP - 1) mx0 = max16(s[0]);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        __asm__ volatile("" : "+v"(q));   // formed here, not where the next iteration needs it
+        tile_barrier();
     };
-
-    u32x4 stage[4];
-    if (grp == 0) {
-        load_k(tile(0), stage);
-        store_k(Ks[0], stage);
-        if (n > 1) {
-            load_k(tile(1), stage);
-            store_k(Ks[1], stage);
-            load_v(tile(1), stage);
-        }
-    } else {
-        load_v(tile(0), stage);
-        store_v(Vs[0], stage);
-        if (n > 2) load_k(tile(2), stage);
+    int it = 1;
+    for (; it + 1 < n; it += 2) {
+        iteration(it, pa, pb, sb);
+        iteration(it + 1, pb, pa, sa);
     }
-    __syncthreads();
-    i32x8 kq[2 * C::KS];
-    read_kq<D>(Ks[0], kbase, kq);
-    if (grp == 0) mfma_block8<D, false>(nullptr, vbase, pb, ones, qf, kq, o, lacc, s);
-    // Same phase structure and barrier count as the bf16 kernel: group 1 runs
-    // one phase behind group 0; 2n + 2 barriers per group, the last one after
-    // every LDS read of the segment.  The K operands of the next score product
-    // are read at the top of each iteration: that tile was stored two phases
-    // before the barrier just passed and is overwritten only after the MFMA
-    // block of this iteration.
-    if (grp == 1) {
-        mfma_block8<D, false>(nullptr, vbase, pb, ones, qf, kq, o, lacc, s);
-        __syncthreads();
+    if (it < n) {
+        iteration(it, pa, pb, sb);
+        pa = pb;
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    // The row maximum of tile it + 1 is taken in the MFMA phase of tile it,
-    // right after its products are issued (its VALU work overlaps them; 6%
-    // faster than at the start of the softmax phase); the softmax phase then
-    // only forms the probabilities.
-    for (int it = 0; it < n; ++it) {
-        read_kq<D>(Ks[(it + 1) & 1], kbase, kq);
-        if (it == 0) row_max(tile(0) * BN);
-        exps();
-        if (grp == 0) {
-            if (it >= 1) store_v(Vs[it & 1], stage);
-            if (it >= 1 && it + 1 < n) load_v(tile(it + 1), stage);
-        } else {
-            if (it + 2 < n) store_k(Ks[it & 1], stage);
-            if (it + 3 < n) load_k(tile(it + 3), stage);
-        }
-        __syncthreads();
-        // (the priority raise is worth 15% here: the products issue ahead of
-        // the other wave's softmax)
-        __builtin_amdgcn_s_setprio(1);
-        mfma_block8<D, true>(Vs[it & 1], vbase, pb, ones, qf, kq, o, lacc, s);
-        __builtin_amdgcn_s_setprio(0);
-        if (it + 1 < n) row_max(tile(it + 1) * BN);
-        __syncthreads();
+    // the last tile's values (iteration n's first steps)
+    if (__ballot(alpha != 1.f)) {
+        lacc *= alpha;
+#pragma unroll
+        for (int mb = 0; mb < C::MB; ++mb) o[mb] *= alpha;
     }
-    if (grp == 0) __syncthreads();
+#pragma unroll
+    for (int mb = 0; mb < C::MB; ++mb) o[mb] = mfma8(read_a(mb, n), pa, o[mb]);
+    lacc = mfma4x8(ones, pa, lacc);
+    __syncthreads();   // (the next segment stores into these tiles)
 
     const float l_tot = lacc[0];  // every row of the ones product holds this query's sum
     const float inv = 1.f / l_tot;
@@ -751,8 +766,8 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t (&Ks)[2][
 template <int D, bool BAL>
 __global__ __launch_bounds__(kThreads, 2) void attn_fp8_kernel(AttnArgs a) {
     using C = Fp8Cfg<D>;
-    __shared__ __attribute__((aligned(16))) uint8_t Ks[2][C::KTILE];
-    __shared__ __attribute__((aligned(16))) uint8_t Vs[2][C::VTILE];
+    __shared__ __attribute__((aligned(16))) uint8_t Ks[kBufs * C::KTILE];
+    __shared__ __attribute__((aligned(16))) uint8_t Vs[kBufs * C::VTILE];
     __shared__ uint32_t flag;
     if (!BAL) {
         const int item = (blockIdx.x & 7) * a.items_per_xcd + (blockIdx.x >> 3);
