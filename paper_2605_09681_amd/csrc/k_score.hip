@@ -187,6 +187,14 @@ __device__ __forceinline__ float cosine(double dot, double na, double nb) {
     return (float)(prod == 0.0 ? 0.0 : dot / sqrt(prod));
 }
 
+// Units of at most kGroups column groups have at most one member in a group: its
+// partial is the group's sum, so nothing is summed per group and the head's last
+// workgroup adds the partials itself, in the groups' order -- the same sums bit
+// for bit.  (With short segments the group sums took a memory latency per 64
+// rows: 30 units of 52 tokens, 1320 rows, 48.4 us the launch, 29.9 us without.  A
+// template switch, as a run-time one it cost the other case 0.5 of 21 us at 480P.)
+bool one_member(const ScoreArgs &a) { return a.n_cg <= kGroups; }
+
 // The last workgroup to arrive of arrival group g of listed head li: for every
 // row (u, f, q) the sum of the group's members' partials -- members are the
 // workgroups wi = u * n_cg + cg with wi % kGroups == g, cg = c0, c0 + kGroups,
@@ -227,6 +235,7 @@ __device__ void group_sum(const ScoreArgs &a, int li, int g) {
 // The last workgroup of listed head li: the head's per-row sums T (LDS,
 // lds_rows doubles) from the group sums, groups in order, then the finish by
 // mode.
+template <bool DIRECT>
 __device__ void finish_head(const ScoreArgs &a, int li, double *T, uint64_t *s_keys, float *s_scores,
                             unsigned char *s_forced, unsigned char *s_keep) {
     const int tid = threadIdx.x;
@@ -235,13 +244,25 @@ __device__ void finish_head(const ScoreArgs &a, int li, double *T, uint64_t *s_k
     const sel::Rule rule = sel::rule_of(a, li);
     const int n_rows = a.units * a.n_frames * 2;
     const double *G = a.group + (int64_t)li * kGroups * n_rows;
+    const double *part = a.part + (int64_t)li * n_rows * a.n_cg;   // [u][cg][f][q]
+    const int blk = a.n_frames * 2;
     // groups 0 .. min(n_wg, kGroups) - 1 have members and wrote every row; the
     // others were not written by this call
-    const int n_groups = min(a.units * a.n_cg, kGroups);
+    const int n_groups = DIRECT ? kGroups : min(a.units * a.n_cg, kGroups);
     for (int r = tid; r < n_rows; r += kThreads) {
         double v[kGroups];
+        if constexpr (DIRECT) {
+            const int u = r / blk, c0 = (u * a.n_cg) % kGroups;
+            const double *p = part + (int64_t)u * a.n_cg * blk + (r - u * blk);
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) v[g] = g < n_groups ? get_shared(G + (int64_t)g * n_rows + r) : 0.0;
+            for (int g = 0; g < kGroups; ++g) {
+                const int c = (g - c0 + kGroups) % kGroups;   // the unit's member of group g
+                v[g] = c < a.n_cg ? get_shared(p + (int64_t)c * blk) : 0.0;
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) v[g] = g < n_groups ? get_shared(G + (int64_t)g * n_rows + r) : 0.0;
+        }
         double acc = 0.0;
 #pragma unroll
         for (int g = 0; g < kGroups; ++g)
@@ -305,7 +326,7 @@ __device__ void finish_pooled(const ScoreArgs &a) {
     }
 }
 
-template <bool F32>
+template <bool F32, bool DIRECT>
 __global__ __launch_bounds__(kThreads, 5) void score_kernel(ScoreArgs a) {
     extern __shared__ double dyn[];            // finisher rows (lds_rows), this workgroup's sums (2 n_frames),
                                                // then (selecting) n_seg keys, n_seg floats, 2 n_seg bytes
@@ -385,13 +406,13 @@ __global__ __launch_bounds__(kThreads, 5) void score_kernel(ScoreArgs a) {
     const int n_wg = a.units * a.n_cg, wi = u * a.n_cg + cg, g1 = wi % kGroups;
     uint32_t *cnt = a.counters + (int64_t)li * kCountersPerHead * kCounterStride;
     if (!arrive_last(cnt + g1 * kCounterStride, (uint32_t)((n_wg - g1 + kGroups - 1) / kGroups), &flag)) return;
-    group_sum(a, li, g1);
+    if constexpr (!DIRECT) group_sum(a, li, g1);
     if (!arrive_last(cnt + kGroups * kCounterStride, (uint32_t)min(n_wg, kGroups), &flag)) return;
     double *T = dyn;
     uint64_t *s_keys = (uint64_t *)(dyn + a.lds_rows + nf * 2);
     float *s_scores = (float *)(s_keys + a.n_seg);
     unsigned char *s_forced = (unsigned char *)(s_scores + a.n_seg);
-    finish_head(a, li, T, s_keys, s_scores, s_forced, s_forced + a.n_seg);
+    finish_head<DIRECT>(a, li, T, s_keys, s_scores, s_forced, s_forced + a.n_seg);
     if (a.pooled && a.mode != kScoreModeHistory) {
         uint32_t *pc = a.counters + (int64_t)a.heads.n * kCountersPerHead * kCounterStride;
         if (!arrive_last(pc, (uint32_t)a.heads.n, &flag)) return;
@@ -429,10 +450,15 @@ hipError_t launch_score(const ScoreArgs &a0, bool f32, hipStream_t s) {
     if (a.select) lds += (size_t)a.n_seg * (sizeof(uint64_t) + sizeof(float) + 2);
     lds = (lds + 15) & ~(size_t)15;
     const dim3 grid((unsigned)a.n_cg, (unsigned)a.units, (unsigned)a.heads.n);
-    if (f32)
-        hipLaunchKernelGGL(score_kernel<true>, grid, dim3(kThreads), lds, s, a);
+    const bool direct = one_member(a);
+    if (f32 && direct)
+        hipLaunchKernelGGL((score_kernel<true, true>), grid, dim3(kThreads), lds, s, a);
+    else if (f32)
+        hipLaunchKernelGGL((score_kernel<true, false>), grid, dim3(kThreads), lds, s, a);
+    else if (direct)
+        hipLaunchKernelGGL((score_kernel<false, true>), grid, dim3(kThreads), lds, s, a);
     else
-        hipLaunchKernelGGL(score_kernel<false>, grid, dim3(kThreads), lds, s, a);
+        hipLaunchKernelGGL((score_kernel<false, false>), grid, dim3(kThreads), lds, s, a);
     return hipGetLastError();
 }
 
