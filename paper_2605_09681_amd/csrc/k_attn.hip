@@ -81,7 +81,7 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kThreads = 512;      // 8 waves
 constexpr int kBufs = 4;           // K and V^T tiles in LDS
 constexpr float kSumLimit = 0x1p100f; // a larger sum of probabilities redoes the segment with a running max
-constexpr float kRescaleSlack = 8.f;  // log2 units the running max may lag behind
+constexpr float kRescaleSlack = 8.f;  // log2 units the running max of a redone segment may lag behind
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // raw 32-bit buffer, range checked
 constexpr bf16x2_t kOnes2 = {(__bf16)1.f, (__bf16)1.f};
 
@@ -203,13 +203,10 @@ __device__ __forceinline__ int div_piece(const AttnArgs &a, int j0) {
     return (int)(p >> 32);
 }
 
-// Position of a key tile of a head read in place: its first key j0 and, while
-// j0 is in the history, the kept piece y it starts in, the row r within that
-// piece (j0 = y * P + r) and that row's offset in the cache.  The tile loop
-// advances it by one tile per iteration with a few scalar adds; the page
-// table is read again only where a piece ends (reading it for every tile
-// measured 0.9% slower: each wave's scalar instructions take issue cycles
-// from its own stream).
+// Position of a key tile: its first key j0 and, read in place while j0 is in the
+// history, the kept piece y it starts in, the row r within that piece
+// (j0 = y * P + r) and that row's offset in the cache.  It moves from run to run
+// of full tiles (attn_segment), where the page table is read.
 struct PageCursor {
     int j0, y, r;
     uint32_t off;  // element offset of history row j0 in the head's cache (j0 < kvl)
@@ -532,9 +529,18 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
         // the others go on at kt0 + 1, or at kt0 where the last tile came first
         if (ragged && kt0 < T - 1) cu = cursor_at(kt0 * BN);
         else advance(cu);
-        // (past the segment's end the order goes on over valid tiles, never stored)
+        // (past the segment's end the order goes on over valid tiles, never used; where
+        // the keys fill no tile, over an empty buffer)
         auto fetch = [&]() {
-            if (left == 0 && Tw > 0) next_run(cu);
+            if (left == 0) {
+                if (Tw > 0) {
+                    next_run(cu);
+                } else {
+                    krun = vrun = rsrc(Kq, 0);
+                    soff = 0;
+                    left = 1;
+                }
+            }
             load();
         };
         // (both tiles' loads in flight together)
