@@ -53,7 +53,7 @@
 // the reference, outputs and normaliser follow one iteration later.
 // Bound: both pipes, at the clock that their power holds (480P launch: products in
 // 42% of the cycles at 1.99 GHz, 38% at 2.10 with the products of one wave group
-// beside the softmax of the other).  480P FP8 step 448 -> 428 us.
+// beside the softmax of the other).  480P FP8 step 442 -> 423 us.
 #include "attn_common.h"
 #include "attn_merge.h"
 
@@ -513,14 +513,11 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint
     for (int kk = 0; kk < C::KS; ++kk)
         qf[kk] = qok ? load32(Qh + (size_t)qrow * D + 64 * kk + 32 * hl) : i32x8{};
 
-    // The segment's key tiles: kt0, kt0 + 1, ... (mod T); where the keys end inside
-    // tile T - 1 and it is one of them, it comes first, before the loop, with the
-    // keys past Lk masked; the others are full ones.
+    // the segment's key tiles: kt0, kt0 + 1, ... (mod T)
     const int Lk = head_kvl(a, h) + Lq;
     const int T = (Lk + BN - 1) / BN;
     const int kt0 = (t0 + rot) % T;
-    const bool ragged = Lk % BN != 0 && T - 1 - kt0 < n;
-    const int Tw = max(Lk / BN, 1);   // the tiles that the order wraps over
+    const int ragged = Lk % BN != 0 ? T - 1 : -1;   // the tile that the keys end in
     const uint8_t *K8 = (const uint8_t *)a.Kc + (size_t)h * a.fp8_rows * D;
     const uint8_t *V8 = (const uint8_t *)a.Vc + (size_t)h * a.fp8_rows * D;
 
@@ -537,7 +534,7 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint
             st.k = *(const u32x4 *)(K8 + (size_t)kt * (BN * D) + 16 * tid);
             st.v = *(const u32x4 *)(V8 + (size_t)kt * (BN * D) + 16 * tid);
         }
-        kt = kt + 1 >= Tw ? 0 : kt + 1;
+        kt = kt + 1 >= T ? 0 : kt + 1;
     };
     const int kofs = (tid / C::KCH) * C::KROW + 16 * (tid % C::KCH);
     const int vofs = (tid / C::VCH) * C::VROW + 16 * (tid % C::VCH);
@@ -610,9 +607,8 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint
     // Prologue: tiles 0, 1 and 2 into LDS and registers, then the first tile's
     // probabilities and the second one's scores.
     Stage sa = {}, sb = {}, sc3 = {};
-    kt = ragged ? T - 1 : kt0;
+    kt = kt0;
     fetch(sa);
-    if (ragged && kt0 < T - 1) kt = kt0;
     fetch(sb);
     fetch(sc3);
     store(0, sa);
@@ -626,7 +622,8 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint
 #pragma unroll
         for (int kk = 0; kk < C::KS; ++kk)
             s[kb] = mfma8(load32(Ks + kbase + kb * 32 * C::KROW + 64 * kk), qf[kk], kk == 0 ? f32x16_t{} : s[kb]);
-    if (ragged) {
+    // keys past Lk score -inf
+    auto mask = [&]() {
         const int room = Lk - 1 - ((T - 1) * BN + 4 * hl);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -635,7 +632,9 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint
                 const uint32_t past = (uint32_t)((room - (kb * 32 + 8 * (i >> 2) + (i & 3))) >> 31);
                 s[kb][i] = __uint_as_float((past & 0xff800000u) | (~past & __float_as_uint(s[kb][i])));
             }
-    }
+    };
+    int kc = kt0;   // the tile whose scores s holds
+    if (kc == ragged) mask();
     m_run = both(fmaxf(max16(s[0]), max16(s[1]))) * c2;
     bias = kPBias - m_run;
 #pragma unroll
@@ -658,13 +657,18 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint
 
     // One iteration; p: the tile before's probabilities, q: this tile's.
     auto iteration = [&](int it, i32x8 &p, i32x8 &q, Stage &st) {
-        // the running max moves where the tile's exceeds it by more than kSlack;
+        // the running max moves where a row's exceeds it by more than kSlack;
         // what it scales follows one iteration later, when the value products up to
         // the tile before are in
         if (__ballot(alpha != 1.f)) {
             lacc *= alpha;
 #pragma unroll
             for (int mb = 0; mb < C::MB; ++mb) o[mb] *= alpha;
+        }
+        kc = kc + 1 >= T ? 0 : kc + 1;
+        if (kc == ragged) {
+            mask();
+            mx0 = max16(s[0]);
         }
         float mx = 0.f;
 #pragma unroll
@@ -680,7 +684,8 @@ __device__ __forceinline__ void fp8_segment(const AttnArgs &a, uint8_t *Ks, uint
             }
             if (x == 0) {
                 mx = both(fmaxf(mx0, max16(s[1]))) * c2;
-                const float m_new = mx > m_run + kSlack ? mx : m_run;
+                const bool move = __ballot(mx > m_run + kSlack) != 0;
+                const float m_new = move ? fmaxf(m_run, mx) : m_run;
                 alpha = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
                 bias = kPBias - m_run;
