@@ -47,10 +47,10 @@
 // instructions per tile and its wait for the second part of a straddling tile
 // were in the way).  1080P layer step 12.60 -> 12.08 ms, 480P 528 -> 508 us, with
 // quarter-frame segments, where every sixth tile straddles, 452 -> 425 us.
-// Measured beside it (480P step, same box): the wave groups half an iteration
-// apart 544 against 527 us; loads issued a whole run of scalar branches after the
-// tile's last product 527 against 508 us (a run of full tiles now costs a scalar
-// add); the exponentials in the second half of an iteration 572 us.
+// Measured beside it, 480P step: the wave groups half an iteration apart 544
+// against 527 us; every tile's source found anew by scalar branches 527 against
+// 508 us (a run of full tiles now costs a scalar add); all exponentials in the
+// second half of an iteration 571 against 557 us of the kernel before.
 //
 // Global K/V rows come in through buffer loads whose per-lane offsets are loop
 // invariant; rows past the end of a source fall outside the buffer's range and
