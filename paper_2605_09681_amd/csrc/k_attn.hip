@@ -741,7 +741,12 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
         finish_tile();
         l_run += l2;
 
-        if (every) break;
+        if (every) {
+            // (a workgroup whose range goes on stores the next segment's first tiles
+            // into buffers that a slower wave may still read here)
+            __syncthreads();
+            break;
+        }
         // redo?
         float z = 0.f;
 #pragma unroll
