@@ -81,6 +81,7 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kThreads = 512;      // 8 waves
 constexpr int kBufs = 4;           // K and V^T tiles in LDS
 constexpr float kSumLimit = 0x1p100f; // a larger sum of probabilities redoes the segment with a running max
+constexpr float kLowest = 0x1.fffffep127f;  // largest finite value
 constexpr float kRescaleSlack = 8.f;  // log2 units the running max of a redone segment may lag behind
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // raw 32-bit buffer, range checked
 constexpr bf16x2_t kOnes2 = {(__bf16)1.f, (__bf16)1.f};
@@ -668,7 +669,9 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
                     s[kb][i] = __uint_as_float((past & 0xff800000u) | (~past & __float_as_uint(s[kb][i])));
                 }
         }
-        m_run = row_max(s[0], s[1]);
+        // A row whose scores here are all -inf takes the lowest finite reference: its
+        // keys weigh nothing, and the first other ones overflow its sum.
+        m_run = fmaxf(row_max(s[0], s[1]), -kLowest);
         set_m();
 #pragma unroll
         for (int p = 0; p < kLate; ++p) {
@@ -762,8 +765,9 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
     }
 
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    const float inv = 1.f / l_tot;
+    float inv = 1.f / l_tot;
     if (slot) {
+        if (l_tot == 0.f) inv = 0.f;   // a part whose keys all score -inf: weight 0, not 0 * inf
         // device-scope stores: the workgroup that merges the item may run on
         // another XCD, within this launch
         unsigned long long *op = (unsigned long long *)slot;

@@ -179,3 +179,31 @@ def test_levels_above_the_reference(d, span, schedule):
     x = _Inputs(schedule, d, int(d + span), keys, queries)
     want = x.reference()
     _check(x.run(), want, want[3])
+
+
+@pytest.mark.parametrize("schedule", SCHEDULES)
+@pytest.mark.parametrize("base", [0.0])
+@pytest.mark.parametrize("mask", [float("-inf"), -3.3895313892515355e38])
+def test_keys_with_the_lowest_scores(mask, base, schedule):
+    """Keys that weigh nothing -- -inf, a bf16 lowest value whose products overflow
+    to it, or a large negative value -- where they fill whole tiles and parts: the
+    ragged last tile, the chunk's first 150 rows, every third frame.  The other
+    scores lie around `base` nats, so a reference of 0 would not hold them."""
+    print(f"[gpu case] attention-lowest mask={mask} base={base} schedule={schedule}", flush=True)
+    d = 64 if schedule == "ranges" and base else 128
+
+    def queries(g, n):
+        return (torch.rand(n, LQ, d, generator=g) + 0.5).bfloat16()              # every product has the mask's sign
+
+    def keys(g, n, kept):
+        k = torch.randn(n, H * F + LQ, d, generator=g) * 0.3 + base / math.sqrt(d)
+        k[:, H * F:H * F + 150] = mask
+        k[:, -63:] = mask
+        k[:, :H * F].view(n, H, F, d)[:, ::3] = mask
+        k = k.bfloat16()
+        return k[:, :H * F].contiguous(), k[:, H * F:].contiguous()
+
+    x = _Inputs(schedule, d, int(200 + base), keys, queries)
+    want = x.reference()
+    assert want[0].isfinite().all()
+    _check(x.run(), want, want[3])
