@@ -81,6 +81,7 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kThreads = 512;      // 8 waves
 constexpr int kBufs = 4;           // K and V^T tiles in LDS
 constexpr float kSumLimit = 0x1p100f; // a larger sum of probabilities redoes the segment with a running max
+constexpr float kFarMove = 64.f;      // largest move by whole powers of two
 constexpr float kLowest = 0x1.fffffep127f;  // largest finite value
 constexpr float kRescaleSlack = 8.f;  // log2 units the running max of a redone segment may lag behind
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // raw 32-bit buffer, range checked
@@ -608,6 +609,13 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
             for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s1[i]);
             return fmaxf(mx, __shfl_xor(mx, 32)) * c2;
         };
+        // A finite reference above every score of a row maximum mx: the rounding of a
+        // score times c2 passes the exponent by half a step, which overflows it where
+        // a step of mx is large (scores of -1e30).
+        auto above = [](float mx) {
+            mx = fmaxf(mx, -kLowest);
+            return mx <= kLowest ? fminf(fmaf(fabsf(mx), 0x1p-23f, mx), kLowest) : mx;
+        };
         // Pair of probabilities formed in step x: those of key block 0 from its
         // second step after run A on, those of key block 1 from the second after run
         // C; the last ones (from kLate on) in run A of the next iteration.
@@ -671,7 +679,8 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
         }
         // A row whose scores here are all -inf takes the lowest finite reference: its
         // keys weigh nothing, and the first other ones overflow its sum.
-        m_run = fmaxf(row_max(s[0], s[1]), -kLowest);
+        m_run = row_max(s[0], s[1]);
+        m_run = every ? above(m_run) : fmaxf(m_run, -kLowest);
         set_m();
 #pragma unroll
         for (int p = 0; p < kLate; ++p) {
@@ -690,17 +699,20 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
         while (it < n) {
             if (every) {
                 // The running max moves where this tile's exceeds it by more than
-                // kRescaleSlack, by whole powers of two; what the previous tile still has
-                // to do takes the new one.
+                // kRescaleSlack, by whole powers of two (what is scaled stays as it was
+                // rounded), or to the tile's own beyond kFarMove, where a sum with the
+                // difference would lose it; what the previous tile still has to do takes
+                // the new one.
                 run(0, xB);
                 float mx = row_max(s[0], s[0]);
 #pragma unroll
                 for (int kk = 0; kk < C::KS; ++kk)
                     s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_a(xC + kk, it), qf[kk],
                                                                    kk == 0 ? f32x16_t{} : s[0], 0, 0, 0);
-                mx = fmaxf(mx, row_max(s[0], s[0]));
+                mx = above(fmaxf(mx, row_max(s[0], s[0])));
                 if (__ballot(mx > m_run + kRescaleSlack)) {
-                    const float up = mx > m_run + kRescaleSlack ? ceilf(mx - m_run) : 0.f;
+                    const bool move = mx > m_run + kRescaleSlack, far = move && mx - m_run > kFarMove;
+                    const float up = far ? mx - m_run : move ? ceilf(mx - m_run) : 0.f;
                     const float alpha = __builtin_amdgcn_exp2f(-up);
                     l_run *= alpha;
                     l2 *= alpha;
@@ -713,7 +725,7 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
                         e1 *= alpha;
                         round_pair(p);
                     }
-                    m_run += up;
+                    m_run = far ? mx : m_run + up;
                 }
             }
             set_m();

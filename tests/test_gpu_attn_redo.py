@@ -182,8 +182,8 @@ def test_levels_above_the_reference(d, span, schedule):
 
 
 @pytest.mark.parametrize("schedule", SCHEDULES)
-@pytest.mark.parametrize("base", [0.0])
-@pytest.mark.parametrize("mask", [float("-inf"), -3.3895313892515355e38])
+@pytest.mark.parametrize("base", [0.0, 150.0, -150.0])
+@pytest.mark.parametrize("mask", [float("-inf"), -3.3895313892515355e38, -1e30])
 def test_keys_with_the_lowest_scores(mask, base, schedule):
     """Keys that weigh nothing -- -inf, a bf16 lowest value whose products overflow
     to it, or a large negative value -- where they fill whole tiles and parts: the
