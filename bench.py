@@ -308,7 +308,7 @@ def timed_steps(cfg, layers, bufs, slots, args, mode):
     import numpy as np
     import torch
     stream = torch.cuda.current_stream()
-    names = ("attention",) if mode in ("paged", "serial") else ("static_attention", "dynamic_attention")
+    names = ("attention",) if mode == "serial" else layers[0].attention_launches()
     events = [{n: (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for n in names}
               for _ in range(args.steps)]
 
@@ -361,7 +361,8 @@ def launch_rooflines(cfg, layer, launch_ms, traffic, mode):
                                         "read in place)"},
         "compact": {"static_attention": f"fkv_chunk_attention_static: {paged} (static heads, in place)",
                     "dynamic_attention": f"fkv_chunk_attention_heads: {plain} (dynamic heads, compacted "
-                                         "history)"},
+                                         "history)",
+                    "attention": f"fkv_chunk_attention: {plain} (all heads, compacted history)"},
         "serial": {"attention": f"fkv_chunk_attention: {plain} (all heads, compacted history)"},
     }[mode]
     out = []

@@ -226,12 +226,19 @@ class CompressedLayer:
                                   Q, K_cur, V_cur, self.scale, O, lse,
                                   self.attn_workspace if workspace is None else workspace, head_list)
 
+    def attention_launches(self):
+        """Names of the attention launches of one :meth:`step`: "attention" for
+        one launch, "static_attention" and "dynamic_attention" for the
+        two-stream steps."""
+        two = self.side is not None if self.step_mode == "paged2" else self.step_mode == "compact" and self.two_streams
+        return ("static_attention", "dynamic_attention") if two else ("attention",)
+
     def step(self, K_hist, V_hist, frame_slot, Q, K_cur, V_cur, O, lse=None, events=None):
         """One AR step of the layer (see the module docstring for the modes).
-        ``events`` (optional) maps a launch name to a pair of torch.cuda.Events
-        recorded around that attention launch on the stream it runs on
-        ("attention" for one launch, "static_attention" and "dynamic_attention"
-        for the two-stream steps), for per-launch timing."""
+        ``events`` (optional) maps a launch name of :meth:`attention_launches`
+        to a pair of torch.cuda.Events recorded around that attention launch on
+        the stream it runs on, for per-launch timing; the step is the same with
+        and without them."""
         def mark(name, i, stream):
             if events is not None and name in events:
                 events[name][i].record(stream)
@@ -259,8 +266,7 @@ class CompressedLayer:
             mark("dynamic_attention", 1, main)
             main.wait_stream(self.side)
             return
-        two = self.two_streams
-        if self.side is None or not (two or events):
+        if not self.two_streams:
             cur = torch.cuda.current_stream(self.device)
             if self.static_in_place and not self.has_dynamic:
                 mark("attention", 0, cur)
@@ -274,9 +280,8 @@ class CompressedLayer:
             return
         main = torch.cuda.current_stream(self.device)
         args = (self.Kc, self.Vc, self.kv_len, K_cur, V_cur, self.scale, O, lse)
-        side = self.side if two else main
-        if two:
-            side.wait_stream(main)
+        side = self.side
+        side.wait_stream(main)
         with torch.cuda.stream(side):
             if self.static_in_place:
                 mark("static_attention", 0, side)
@@ -288,17 +293,15 @@ class CompressedLayer:
                 fkv_chunk_attention_heads(self.shape, self.static_heads, Q, *args[:7], lse=lse,
                                           workspace=self.attn_workspace2)
                 mark("static_attention", 1, side)
-        if two:
-            for t in (K_hist, V_hist, Q, K_cur, V_cur, O) + ((lse,) if lse is not None else ()):
-                t.record_stream(side)
+        for t in (K_hist, V_hist, Q, K_cur, V_cur, O) + ((lse,) if lse is not None else ()):
+            t.record_stream(side)
         self.score(K_hist, frame_slot, K_cur)
         self.select_compact(K_hist, V_hist, frame_slot)
         mark("dynamic_attention", 0, main)
         fkv_chunk_attention_heads(self.shape, self.dynamic_heads, Q, *args[:7], lse=lse,
                                   workspace=self.attn_workspace)
         mark("dynamic_attention", 1, main)
-        if two:
-            main.wait_stream(side)
+        main.wait_stream(side)
 
 
 class HeadProfiler:
