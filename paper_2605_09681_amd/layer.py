@@ -30,7 +30,7 @@ synchronises with the host.
 from __future__ import annotations
 
 import math
-from typing import Optional, Sequence
+from typing import Optional, Sequence, Union
 
 import torch
 
@@ -63,12 +63,14 @@ def paged_supported(dtype, frame_tokens: int, seg_tokens: int, cap_frames: int) 
 # the static heads on a second stream, next to the scoring and the compaction.
 # The two stream waits cost about 60 us of host time and keep the GPU from
 # running the launches back to back; they hide the scoring and the compaction.
-# Two streams against one: 83 KB 139 and 57 us, 2.4 MB 244 and 240, 5 MB 128 and
-# 61, 15 MB 127 and 84; 53 MB 556 and 592, 88 MB 278 and 315, 140 MB 3225 and
-# 3283.  fp32 steps, whose attention is far longer than all the rest, measured
-# the same or slower with two (26 MB 381-405 and 394, 106 MB 4900 and 4705), and
-# so did compress(), which has no attention to hide behind (53 MB 124 and 90,
-# 276 MB 472 and 470): these always take one.
+# A layer step, two streams against one, us: 83 KB of keys 139 and 57, 6.7 MB 110
+# and 68, 17 MB 351 and 345, 26 MB 210 and 200, 53 MB 592 and 604, 70 MB 650 and
+# 666.  A rollout's layer: 0.1 MB 116 and 61, 6.7 MB 126 and 66, 17 MB 327 and
+# 320, 26 MB 198 and 189, 53 MB 586 and 559.  fp32 steps, whose attention is far
+# longer than all the rest, measured the same or slower with two (12 MB 274 and
+# 277, 26 MB 381-405 and 394, 106 MB 4900 and 4705), and so did compress(), which
+# has no attention to hide behind (53 MB 124 and 90, 276 MB 472 and 470): these
+# take one unless told otherwise.
 OVERLAP_BYTES = 20 << 20
 
 
@@ -81,8 +83,13 @@ class CompressedLayer:
     def __init__(self, n_heads: int, head_dim: int, frame_tokens: int, hist_frames: int,
                  cap_frames: int, chunk_frames: int, seg_tokens: int, dtype: str,
                  budgets: Sequence, device="cuda", slab: Optional[int] = None,
-                 balanced: bool = True, overlap: bool = True, in_place: Optional[bool] = None,
+                 balanced: bool = True, overlap: Union[bool, str] = True, in_place: Optional[bool] = None,
                  step_mode: Optional[str] = None):
+        """``overlap`` (compacting steps): True runs the static heads on a second
+        stream where that pays (OVERLAP_BYTES), "always" at every size and in
+        :meth:`compress` too, False never.  ``in_place``: whether step() attends
+        the static heads in place; True asks for it at every size (on the second
+        stream), None leaves it to the route."""
         if len(budgets) != n_heads:
             raise ValueError(f"{len(budgets)} head budgets for {n_heads} heads")
         self.shape = make_shape(n_heads, head_dim, frame_tokens, hist_frames, cap_frames,
@@ -116,9 +123,10 @@ class CompressedLayer:
         # side stream for the static heads (only when both head types exist)
         self.side = (torch.cuda.Stream(device=dev) if overlap and self.has_static and self.has_dynamic
                      else None)
+        self.always = self.side is not None and overlap == "always"
         # (a caller's slab may hold the dynamic heads alone: then there is no room to gather static ones)
         self.two_streams = self.side is not None and (
-            self.slab < slab_tokens(self.shape, self.heads)
+            self.always or in_place is True or self.slab < slab_tokens(self.shape, self.heads)
             or _overlap_pays(self.types, hist_frames, frame_tokens, head_dim, self.dtype))
         self.static_heads = [h for h, t in enumerate(self.types) if t == FKV_STATIC]
         self.dynamic_heads = [h for h, t in enumerate(self.types) if t == FKV_DYNAMIC]
@@ -202,6 +210,17 @@ class CompressedLayer:
 
     # whole step --------------------------------------------------------------
     def compress(self, K_hist, V_hist, frame_slot, K_cur):
+        if self.always:
+            main = torch.cuda.current_stream(self.device)
+            self.side.wait_stream(main)             # inputs written on the main stream
+            with torch.cuda.stream(self.side):
+                self.compress_static(K_hist, V_hist, frame_slot)
+            for t in (K_hist, V_hist):              # read on the side stream too
+                t.record_stream(self.side)
+            self.score(K_hist, frame_slot, K_cur)
+            self.select_compact(K_hist, V_hist, frame_slot)
+            main.wait_stream(self.side)             # attention reads every head's Kc/Vc/kv_len
+            return
         if self.has_dynamic:
             self.score(K_hist, frame_slot, K_cur)
             self.select_compact(K_hist, V_hist, frame_slot)
@@ -351,7 +370,9 @@ class RolloutStack:
     the first one).  Per layer and AR step :meth:`run_layer` either (step_mode
     "paged", the default where the shape allows it) scores and selects the
     dynamic heads in one launch and then attends every head in one launch with
-    its kept history read in place from the cache, or ("compact") runs the
+    its kept history read in place from the cache, or ("compact") gathers every
+    head and attends them in one launch -- or, where two streams pay
+    (OVERLAP_BYTES; ``overlap="always"`` at every size, False never), runs the
     static heads' attention on a side stream (read in place for bf16 and
     frames of at least 64 tokens, else gathered first) next to the dynamic
     heads' scoring, compaction and attention.  With a shared score row from
@@ -368,7 +389,7 @@ class RolloutStack:
 
     def __init__(self, n_layers: int, n_heads: int, head_dim: int, frame_tokens: int, window: int,
                  chunk_frames: int, seg_tokens: int, dtype: str = "bf16", device="cuda",
-                 overlap: bool = True, step_mode: Optional[str] = None):
+                 overlap: Union[bool, str] = True, step_mode: Optional[str] = None):
         self.n_layers, self.n_heads, self.d = n_layers, n_heads, head_dim
         self.F, self.window, self.C, self.L = frame_tokens, window, chunk_frames, seg_tokens
         self.dtype_name = dtype
@@ -398,6 +419,7 @@ class RolloutStack:
         self.attn_ws2 = torch.zeros_like(self.attn_ws) if (n > 0 and overlap) else None
         self.scale = 1.0 / math.sqrt(head_dim)
         self.side = torch.cuda.Stream(device=dev) if overlap else None
+        self.always = overlap == "always"
         self.static_in_place = static_in_place_supported(dtype, frame_tokens)
         can_paged = paged_supported(dtype, frame_tokens, seg_tokens, window)
         if step_mode is None:
@@ -468,11 +490,9 @@ class RolloutStack:
 
     def run_layer(self, layer: int, budgets, frame_slot, Q, K_cur, V_cur, O, lse=None, pooled=None,
                   incremental: bool = False):
-        """One AR step of one layer: compress its cache, then chunk attention
-        into O -- the static heads (attended in place, or gathered and then
-        attended) on the side stream while the dynamic heads are scored,
-        compacted and attended on the current stream.  ``pooled`` (a row from :meth:`score_pooled`)
-        replaces the layer's own per-head scoring."""
+        """One AR step of one layer, chunk attention into O by the stack's step
+        mode (see the class docstring).  ``pooled`` (a row from
+        :meth:`score_pooled`) replaces the layer's own per-head scoring."""
         H = len(frame_slot)
         shape = self.shape(H)
         heads, key = self._budget_array(budgets)
@@ -497,7 +517,7 @@ class RolloutStack:
             return
         main = torch.cuda.current_stream(self.device)
         side = self.side if (self.side is not None and has_static and has_dynamic) else None
-        if not _overlap_pays(types, H, self.F, self.d, Kh.dtype):
+        if not (self.always or _overlap_pays(types, H, self.F, self.d, Kh.dtype)):
             side = None
         att = (self.Kc, self.Vc, self.kv_len, K_cur, V_cur, self.scale, O)
         if side is not None:

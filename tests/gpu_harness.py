@@ -46,12 +46,12 @@ def dev_inputs(x: W.LayerInputs):
                 V_cur=to_dev(x.V_cur, dt), Q=to_dev(x.Q, dt))
 
 
-def make_layer(cfg: W.LayerConfig, heads=None, slab=None, balanced=True, in_place=None, step_mode=None):
+def make_layer(cfg: W.LayerConfig, heads=None, slab=None, balanced=True, in_place=None, step_mode=None, overlap=True):
     from paper_2605_09681_amd.layer import CompressedLayer
     return CompressedLayer(cfg.n_heads, cfg.head_dim, cfg.frame_tokens, cfg.hist_frames,
                            cfg.cap_frames, cfg.chunk_frames, cfg.seg_tokens, cfg.dtype,
                            cfg.heads if heads is None else heads, slab=slab, balanced=balanced,
-                           in_place=in_place, step_mode=step_mode)
+                           overlap=overlap, in_place=in_place, step_mode=step_mode)
 
 
 def run_gpu(cfg: W.LayerConfig, x: W.LayerInputs, heads=None, with_lse=True, scale=None,

@@ -42,3 +42,28 @@ def test_events_time_the_step_that_runs(dtype, two):
         got.append((O, lse, layer.scores, layer.kept_seg, layer.kv_len, layer.Kc, layer.Vc))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def test_the_caller_chooses_the_route():
+    """Small layers take one stream by themselves; overlap="always", an explicit
+    in_place=True or a slab without room for the static heads takes two."""
+    cfg, x = _small()
+    heads = (W.HeadBudget(W.STATIC, 1, 6),) + cfg.heads[1:]          # keeps all 700 tokens, the dynamic heads 400
+    route = lambda **kw: make_layer(cfg, heads, step_mode="compact", **kw).two_streams
+    assert not route() and not route(overlap=False) and not route(in_place=False) and not route(slab=700)
+    assert route(overlap="always") and route(in_place=True) and route(slab=400)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_compress_on_two_streams(dtype):
+    """compress() with overlap="always": the bytes of the one-stream call."""
+    cfg, x = _small(dtype)
+    d = dev_inputs(x)
+    got = []
+    for overlap in (True, "always"):
+        layer = make_layer(cfg, step_mode="compact", overlap=overlap)
+        layer.compress(d["K_hist"], d["V_hist"], x.frame_slot, d["K_cur"])
+        torch.cuda.synchronize()
+        got.append((layer.scores, layer.kept_seg, layer.kv_len, layer.Kc, layer.Vc))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)

@@ -162,13 +162,19 @@ def test_480p_many_segments():
     check_layer(cfg, x, rows=sample_rows(cfg.lq, 8, seed=15))
 
 
-@pytest.mark.parametrize("case", ["small", "small-d64", "small-f32", "480p", "480p-gather", "1080p"])
+@pytest.mark.parametrize("case", ["small", "small-one", "small-d64", "small-d64-one", "small-f32", "small-f32-one",
+                                  "480p", "480p-gather", "1080p"])
 def test_pipelined_step(case):
-    """CompressedLayer.step: the static heads' attention on a side stream --
-    read in place from the cache (bf16), or gathered first (fp32, and the
-    480p-gather case) -- while the dynamic heads are scored, compacted and
-    attended on the main stream, each stream with its own workspace.  Same
-    parity bar as the serial path; the small case interleaves head types."""
+    """CompressedLayer.step of a compacting layer, both routes.  Two streams: the
+    static heads' attention on a side stream -- read in place from the cache
+    (bf16), or gathered first (fp32, and the 480p-gather case) -- while the
+    dynamic heads are scored, compacted and attended on the main stream, each
+    stream with its own workspace.  One stream (the "-one" cases, what small and
+    fp32 steps take by themselves): every head gathered and attended in one
+    launch.  Same parity bar as the serial path; the small cases interleave head
+    types."""
+    one = case.endswith("-one")
+    case = case.removesuffix("-one")
     if case.startswith("small"):
         cfg = _small(F=100, L=25, d=64 if case == "small-d64" else 128, dtype="f32" if case == "small-f32" else "bf16")
         x = W.make_layer_inputs(cfg, seed=30, frame_slot=np.array([3, 0, 8, 1, 5, 2, 7], np.int32))
@@ -179,7 +185,9 @@ def test_pipelined_step(case):
         x = W.make_layer_inputs(cfg, seed=31, frame_slot=slot)
         rows = sample_rows(cfg.lq, 8 if case != "1080p" else 4, seed=31)
     _print_case("pipelined-step", case=case)
-    layer = make_layer(cfg, in_place=False if case == "480p-gather" else None, step_mode="compact")
+    layer = make_layer(cfg, in_place=False if case == "480p-gather" else None, step_mode="compact",
+                       overlap="always" if case.startswith("small") and not one else True)
+    assert layer.two_streams == (not one)
     assert layer.side is not None and (cfg.dtype == "f32" or layer.attn_workspace2 is not None)
     assert layer.static_in_place == (cfg.dtype == "bf16" and case != "480p-gather")
     d = dev_inputs(x)
@@ -188,7 +196,7 @@ def test_pipelined_step(case):
     layer.step(d["K_hist"], d["V_hist"], x.frame_slot, d["Q"], d["K_cur"], d["V_cur"], O, lse)
     torch.cuda.synchronize()
     ref = oracle.run_layer(cfg, x, rows=rows, scale=1 / math.sqrt(cfg.head_dim))
-    assert_compression_exact(cfg, layer, ref, skip_static=layer.static_in_place)
+    assert_compression_exact(cfg, layer, ref, skip_static=layer.static_in_place and not one)
     assert_attention_close(O, ref, cfg.dtype, lse)
 
 
@@ -737,8 +745,9 @@ def _stack_budgets(mask_row, H, F, L):
                  W.HeadBudget(W.STATIC, 1, 2) for m in mask_row)
 
 
+@pytest.mark.parametrize("overlap", [True, "always"])
 @pytest.mark.parametrize("pooled,incremental", [(False, False), (True, False), (False, True), (True, True)])
-def test_rollout_stack(pooled, incremental):
+def test_rollout_stack(pooled, incremental, overlap):
     """RolloutStack: 3 layers with their own head masks and rolling caches
     (window 7, sink pinned, 2-frame chunks) over 6 chunks of 2 AR steps, across
     the ring wrap, sharing one set of compressed buffers.  Every layer's step is
@@ -747,14 +756,16 @@ def test_rollout_stack(pooled, incremental):
     pooled over all heads of layer 0 (the first-block proxy); with
     incremental=True the scores come from per-chunk history statistics plus
     the pair touching the chunk (fkv_score_history once per chunk,
-    fkv_score_segments_cached every step)."""
+    fkv_score_segments_cached every step).  The layers compact (L < 64), at this
+    size on one stream, with overlap="always" on two."""
     import paper_2605_09681_amd as fkv
     from paper_2605_09681_amd.layer import RolloutStack
     from types import SimpleNamespace
     n_layers, nh, d, F, window, C, L = 3, 4, 64, 64, 7, 2, 32
     n_chunks, n_steps = 6, 2
     masks = W.rollout_head_masks(21, n_layers=n_layers, n_heads=nh, n_dynamic=2)
-    stack = RolloutStack(n_layers, nh, d, F, window, C, L)
+    stack = RolloutStack(n_layers, nh, d, F, window, C, L, overlap=overlap)
+    assert stack.step_mode == "compact"
     K_o = np.zeros((n_layers, nh, window, F, d), np.uint16)
     V_o = np.zeros_like(K_o)
     for i in range(n_chunks):
@@ -790,10 +801,10 @@ def test_rollout_stack(pooled, incremental):
                 x = W.LayerInputs(cfg, K_o[layer], V_o[layer], Kq, Vq, Q, slots)
                 scores, kept = stack.views(H)
                 got = SimpleNamespace(kv_len=stack.kv_len, scores=scores, kept_seg=kept, Kc=stack.Kc, Vc=stack.Vc)
-                assert stack.static_in_place   # static heads attended in place: Kc/Vc rows not written
+                assert stack.static_in_place   # (two streams: static heads' Kc/Vc rows not written)
                 if row is None:
                     ref = oracle.run_layer(cfg, x, scale=1 / math.sqrt(d))
-                    assert_compression_exact(cfg, got, ref, skip_static=True)
+                    assert_compression_exact(cfg, got, ref, skip_static=overlap == "always")
                 else:
                     ref = oracle.run_layer(cfg, x, scale=1 / math.sqrt(d), attention=False)
                     kept_d, kv_d = from_dev(kept), from_dev(stack.kv_len)
