@@ -1,5 +1,6 @@
-"""Attention mass at the sizes where its bins and tiles can go wrong: bins
-shorter than, equal to and just past a 64-key tile, histories that are not a
+"""Attention mass at the sizes where its bins and tiles can go wrong: bins that
+share a 64-key tile (up to 32 keys), bins shorter than, equal to and just past
+one, histories that are not a
 whole number of bins, more bins than keys, several query tiles, accumulation."""
 import math
 
@@ -10,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("F,C", [(1, 5), (63, 1), (64, 5), (65, 4), (130, 3)])
+@pytest.mark.parametrize("F,C", [(1, 5), (1, 300), (2, 40), (3, 7), (21, 13), (31, 9), (32, 9), (33, 8), (63, 1), (64, 5), (65, 4), (130, 3)])
 def test_mass_edges(d, F, C):
     """Every head's mass against fp64 softmax column sums.  The probabilities
     are fp32 exponentials of fp32 score sums (|z| < 32, so each is within
