@@ -75,7 +75,6 @@ using namespace attn;
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 512;      // 8 waves
@@ -642,7 +641,6 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // the value products of key block 1 of the tile before
         // (m_exp opaque in every iteration: else the compiler takes the exponentials
         // that both ways on from an iteration begin with into its end)
         auto set_m = [&]() {
@@ -651,6 +649,7 @@ __device__ __forceinline__ void attn_segment(const AttnArgs &a, uint16_t *Ks, ui
         };
         // P formed here, not where the next iteration first needs it
         auto pin_p = [&](int t) { __asm__ volatile("" : "+v"(pb[t])); };
+        // the value products of key block 1 of the tile before
         auto finish_tile = [&]() {
             set_m();
 #pragma unroll
