@@ -207,3 +207,31 @@ def test_keys_with_the_lowest_scores(mask, base, schedule):
     want = x.reference()
     assert want[0].isfinite().all()
     _check(x.run(), want, want[3])
+
+
+@pytest.mark.parametrize("schedule", SCHEDULES)
+def test_infinities_and_nan_in_recomputed_segments(schedule):
+    """An infinite or NaN value, and a NaN query, reach what they weigh in and
+    nothing else, whichever segments are computed again for them."""
+    print(f"[gpu case] attention-infinities schedule={schedule}", flush=True)
+    d = 64
+
+    def queries(g, n):
+        q = torch.randn(n, LQ, d, generator=g).bfloat16()
+        q[2, 5, 0] = float("nan")
+        return q
+
+    def keys(g, n, kept):
+        return torch.randn(n, H * F, d, generator=g).bfloat16(), torch.randn(n, LQ, d, generator=g).bfloat16()
+
+    x = _Inputs(schedule, d, 11, keys, queries)
+    x.Vq[0, 130, 7], x.Vq[1, 100, 3] = float("inf"), float("nan")
+    O, lse = x.run()
+    bad = torch.zeros_like(O, dtype=torch.bool)
+    bad[0, :, 7] = bad[1, :, 3] = bad[2, 5] = True
+    assert (O[0, :, 7] == float("inf")).all() and O[1, :, 3].isnan().all() and O[2, 5].isnan().all()
+    assert lse[2, 5].isnan()
+    x.Q, x.Vq = x.Q.nan_to_num(), x.Vq.nan_to_num(posinf=0.0)
+    Ow, lw, bound, zmax = x.reference()
+    O, lse = torch.where(bad, Ow, O), torch.where(bad[:, :, 0], lw, lse)
+    _check((O, lse), (Ow, lw, bound, zmax), zmax)
