@@ -132,33 +132,23 @@ __device__ __forceinline__ Schedule make_schedule(const AttnArgs &a, const WorkL
 }
 
 // Whole parts instead of equal ranges where the chip has workgroups to spare:
-// every item is cut into `parts` (one workgroup each, at most one for every
-// kPartTiles tiles), so no workgroup computes the ends of two items.  A segment costs about
+// every item is cut into `parts` (one workgroup each, at most one per tile), so
+// no workgroup computes the ends of two items.  A segment costs about
 // kSegmentTiles tiles beside its own (the first loads, the first tile's row
 // maxima, the epilogue), and an equal range shorter than an item usually holds
 // two: whole parts win where the longest one is within a segment's cost of an
 // equal range.  0: equal ranges.  (16 heads of 64, 666 query rows, 32 and 44 key
 // tiles per query tile, 48 items: the layer step takes 47.4 us, 53.3 with equal
-// ranges.)  A part costs as much again for its hand-over and its share of the
-// merge, hence kPartTiles: 2 heads of 128, 64 query rows,
-// 4 / 8 / 15 / 26 tiles take 15.0 / 19.0 / 21.0 / 24.0 us, with one part per tile
-// 16.8 / 21.0 / 27.5 / 38.1, of two tiles 16.1 / 18.5 / 22.3 / 27.0, of three
-// 16.1 / 18.5 / 20.6 / 24.4, of six 15.1 / 19.0 / 21.2 / 39.9 (equal ranges).
+// ranges.)
 constexpr int kSegmentTiles = 4;
-constexpr int kPartTiles = 4;
-// parts of an item of T tiles, of at most `parts`
-__device__ __forceinline__ int parts_of(int T, int parts) {
-    return min(parts, (T + kPartTiles - 1) / kPartTiles);
-}
 __device__ __forceinline__ int whole_parts(const AttnArgs &a, const WorkList &wl, const Schedule &sc) {
     const int parts = a.n_blocks / a.n_items;
     if (parts < 2 || sc.total == 0) return 0;
     int longest = wl.T;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) longest = max(longest, __shfl_xor(longest, d, 64));
-    longest = __builtin_amdgcn_readfirstlane(longest);
-    const int n = parts_of(longest, parts);
-    return (longest + n - 1) / n <= (int)(sc.total / sc.G) + kSegmentTiles ? parts : 0;
+    longest = __builtin_amdgcn_readfirstlane((longest + parts - 1) / parts);
+    return longest <= (int)(sc.total / sc.G) + kSegmentTiles ? parts : 0;
 }
 
 // Partial result of one part of an item, in a slot of BM*(D/2 + 2) floats:

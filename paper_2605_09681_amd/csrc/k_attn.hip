@@ -851,7 +851,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnArgs a) {
             li = item / a.n_qtiles;
             qt = item - li * a.n_qtiles;
             const int T = __builtin_amdgcn_readlane(wl.T, li);
-            n_parts = parts_of(T, parts);
+            n_parts = min(parts, T);
             if (j >= n_parts) return;
             t0 = (int)((int64_t)T * j / n_parts);
             t1 = (int)((int64_t)T * (j + 1) / n_parts);

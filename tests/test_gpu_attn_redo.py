@@ -23,7 +23,7 @@ def _kept_frames(schedule):
         return [[0, 20, 1, 19, 2, 5][h % 6] for h in range(48)]
     if schedule == "parts":          # two parts of 18 and 19 tiles
         return [20] * 42
-    return [20, 0, 7, 13]            # one workgroup per item, or parts of three or four tiles
+    return [20, 0, 7, 13]            # one workgroup per item, or parts of one or two tiles
 
 
 def _tiles(kept):
@@ -37,9 +37,9 @@ def _segments(kept):
     items = [t for t in _tiles(kept) for _ in range(QT)]
     total = sum(items)
     parts = G // len(items)
-    count = lambda T: min(parts, -(-T // 4))         # parts of an item: one for every four tiles at most
-    if parts >= 2 and -(-max(items) // count(max(items))) <= total // min(G, total) + 4:
-        cut = [(i, T * j // count(T), T * (j + 1) // count(T), T) for i, T in enumerate(items) for j in range(count(T))]
+    if parts >= 2 and -(-max(items) // parts) <= total // min(G, total) + 4:
+        cut = [(i, T * j // min(parts, T), T * (j + 1) // min(parts, T), T)
+               for i, T in enumerate(items) for j in range(min(parts, T))]
         return [[s] for s in cut], True
     G = min(G, total)
     bases = np.concatenate([[0], np.cumsum(items)])
@@ -69,7 +69,7 @@ def _check_schedule(schedule, kept):
     elif schedule == "parts":
         assert whole and longest > 10
     elif schedule == "short-parts":
-        assert whole and longest == 4
+        assert whole and longest <= 2
 
 
 class _Inputs:
