@@ -148,7 +148,7 @@ __device__ __forceinline__ int whole_parts(const AttnArgs &a, const WorkList &wl
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) longest = max(longest, __shfl_xor(longest, d, 64));
     longest = __builtin_amdgcn_readfirstlane((longest + parts - 1) / parts);
-    return longest <= (int)(sc.total / sc.G) + kSegmentTiles ? parts : 0;
+    return (int64_t)(longest - kSegmentTiles) * sc.G <= sc.total ? parts : 0;   // longest <= total / G + kSegmentTiles
 }
 
 // Partial result of one part of an item, in a slot of BM*(D/2 + 2) floats:

@@ -4,7 +4,7 @@ query tiles, whole and split items; scores whose first tile says nothing about
 the others (the reference of the exponentials is taken from a segment's first
 tile, and a sum or an output that it does not hold is computed again with a
 running maximum); infinities and NaN.  All over a compact copy and with few
-items: the split ones are cut into whole parts of up to four tiles.  Longer
+items: the split ones are cut into whole parts of one or two tiles.  Longer
 parts, equal ranges of tiles and the launch that reads the cache in place are in
 test_gpu_attn_redo.py."""
 import math
