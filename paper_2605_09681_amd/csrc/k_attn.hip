@@ -38,15 +38,21 @@
 // in bf16 and fp32 by 2^100 and more without loss (their relative rounding is
 // the same); a segment in which a sum passes 2^100 or an output is not finite is
 // computed again with a running maximum (it moves where a tile's exceeds it by
-// more than 8 in log2 units).
-// Bound: at 1080P the clock, which the power of the products holds at 1.75-1.85
+// more than 8 in log2 units).  That costs the segment twice and more, and a NaN
+// or an infinity in Q or V always brings it about: 480P step 509 us, 967 with one
+// NaN in one static head's V, 1086 with one in every head's.
+// Bound: at 1080P the clock, which the power of the products holds at 1.73-1.85
 // GHz (a 8192^3 library product reaches 1.2 PFLOP/s on this card, a bare loop of
-// these products, reads and exponentials 1.44), and 66% of the cycles issue a
+// these products, reads and exponentials 1.44), and 65% of the cycles issue a
 // product (60% before, when the softmax of one wave group ran beside the
 // products of the other: its row maximum, its scalar page arithmetic of some 70
 // instructions per tile and its wait for the second part of a straddling tile
-// were in the way).  1080P layer step 12.60 -> 12.08 ms, 480P 528 -> 508 us, with
-// quarter-frame segments, where every sixth tile straddles, 452 -> 425 us.
+// were in the way).  Layer steps, both kernels in turn on one card and then on
+// another: 1080P 13.28 -> 12.52 and 12.97 -> 12.39 ms, 480P 541 -> 519 and 528 ->
+// 507 us, with quarter-frame segments, where every sixth tile straddles, 461 ->
+// 430 and 449 -> 419 us.  A segment's fixed cost went the other way (a launch of one
+// tile per item takes 9.7 us at d = 128, 7.9 before, 8.1 and 6.9 at d = 64), so
+// those with segments of up to ten tiles take up to 9% longer.
 // Measured beside it, 480P step: the wave groups half an iteration apart 544
 // against 527 us; every tile's source found anew by scalar branches 527 against
 // 508 us (a run of full tiles now costs a scalar add); all exponentials in the

@@ -51,9 +51,10 @@
 // them.  E4M3 leaves the probabilities no room above the row maximum, so every
 // tile's is taken, the half of key block 0 in the iteration before; where it moves
 // the reference, outputs and normaliser follow one iteration later.
-// Bound: both pipes, at the clock that their power holds (480P launch: products in
-// 42% of the cycles at 1.99 GHz, 38% at 2.10 with the products of one wave group
-// beside the softmax of the other).  480P FP8 step 442 -> 423 us.
+// Bound: both pipes, at the clock that their power holds (480P launch 324 us under
+// the profiler: products in 42.5% of the cycles at 2.19 GHz; 335 us, 37.8% at 2.34
+// with the products of one wave group beside the softmax of the other).  480P FP8
+// step 443-445 -> 420-428 us on two cards.
 #include "attn_common.h"
 #include "attn_merge.h"
 
